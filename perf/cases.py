@@ -18,11 +18,11 @@ dist      normal, laplace, or student (t with 3 degrees of freedom, 20 % zeros),
           in `segments` contiguous layers of log-uniform scale
 
 A state is a training program's: the step object with a residual carried from
-earlier steps, and the gradients of its next steps.  A pass is one step on the
-next of them.  The four gradients of a state sum to zero (two draws and their
-negatives), so that the residual keeps the spread of a run's first tens of
-steps however often the state is stepped: a cycle with a mean would pile up
-entries just below the threshold, which fresh gradients do not.
+earlier steps, and the gradient.  A pass is one step.  In training every step's
+gradient is a new draw; repeating one, or a short cycle, would pile entries up
+below the threshold or make it swing.  So a state's gradient buffer is longer
+than P n by up to 512 times 32 elements, and each pass steps on the P n elements
+that start 32 further on: every element meets another draw, at no cost.
 """
 
 import math
@@ -124,24 +124,34 @@ def _rows(case):
     return 1 if case["form"] == "row" else case["P"]
 
 
-def _inputs(case, seed, count):
-    """The carried residual (twice the gradients' spread) and `count` gradients, (rows, n) each."""
+def _offsets(case):
+    """How many starts of the gradient in its buffer a state has: layers shift by 1/64 of a row at most."""
+    return 512 if case["segments"] == 1 else max(1, min(512, case["n"] // (64 * 32)))
+
+
+def _inputs(case, seed):
+    """The carried residual (rows, n), of twice the gradients' spread, and the gradient buffer (flat)."""
     gen = torch.Generator(device="cuda").manual_seed(seed)
     scale = _scales(case)
-    out = []
-    for j in range(1 + count):
-        t = torch.empty((_rows(case), case["n"]), dtype=torch.float32, device="cuda")
-        for row in t:
-            _draw_into(row, "normal" if j == 0 else case["dist"], gen)
-            row.mul_(scale)
-        out.append(t.mul_(2.0) if j == 0 else t)
-    return out[0], out[1:]
+    rows, n, more = _rows(case), case["n"], 32 * _offsets(case)
+    resid = torch.empty((rows, n), dtype=torch.float32, device="cuda")
+    for row in resid:
+        row.normal_(generator=gen).mul_(scale).mul_(2.0)
+    buf = torch.empty(rows * n + more, dtype=torch.float32, device="cuda")
+    for w in range(rows):
+        row = buf[w * n:(w + 1) * n]
+        _draw_into(row, case["dist"], gen)
+        row.mul_(scale)
+    _draw_into(buf[rows * n:], case["dist"], gen)
+    buf[rows * n:].mul_(scale[-1])
+    return resid, buf
 
 
 def prepare(case, seed):
     form, P, n, kb = case["form"], case["P"], case["n"], _k_blk(case)
-    resid, (g1, g2) = _inputs(case, seed, 2)
-    s = {"form": form, "grads": [g1, g2, -g1, -g2], "next": 0}
+    resid, buf = _inputs(case, seed)
+    grads = [buf[32 * j:32 * j + resid.numel()].view(resid.shape) for j in range(_offsets(case))]
+    s = {"form": form, "grads": grads, "next": 0}
     if form == "row":
         s.update(P=P, n=n, kb=kb, acc=resid, ws=spardl.workspace(1, P, n, kb),
                  sp_idx=torch.empty((1, P, kb), dtype=torch.int32, device="cuda"),
@@ -252,11 +262,11 @@ def _lazy(A, P, n, kb):
 
 def exact(case, seed):
     form, P, n, d, kb = case["form"], case["P"], case["n"], case["d"], _k_blk(case)
-    A, (g,) = _inputs(case, seed, 1)
+    A, buf = _inputs(case, seed)
     A = A.double()
-    for a, x in zip(A, g):
+    for a, x in zip(A, buf[:A.numel()].view(A.shape)):
         a.add_(x)
-    del g
+    del buf
     if form == "lazy":
         return _lazy(A, P, n, kb)
     Q = P // d
@@ -306,5 +316,4 @@ def exact(case, seed):
         for w, (idx, val) in drops:
             at = final[idx]
             A[w, idx[at]] += val[at]
-    out = {"dense": dense, "acc": A, "local_idx": None, "drop_cnt": None}
-    return out
+    return {"dense": dense, "acc": A, "local_idx": None, "drop_cnt": None}
