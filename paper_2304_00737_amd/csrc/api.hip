@@ -175,8 +175,9 @@ Ws carve(void* ws, size_t ws_bytes, const Layout& L) {
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 inline bool ws_misaligned(const void* ws) { return ((uintptr_t)ws & 255u) != 0; }
 
-// float4 streaming is used when every block start, the row length and the
-// row strides are multiples of 4 and the base pointers are 16-byte aligned.
+// The residual add skips its ragged-edge masks when every block start, the
+// row length and the row strides are multiples of 4 and the base pointers are
+// 16-byte aligned.
 bool blocks_vec4(int64_t n, int32_t P) {
   if (n % 4) return false;
   for (int64_t b = 0; b <= P; ++b)
@@ -266,19 +267,18 @@ struct Fill {
 int topk_units(const float* acc, int64_t ld_acc, int64_t units, const Units& U, int64_t n, int32_t P, int32_t k_blk,
                bool make_hist, bool spec, int32_t* sp_idx, float* sp_val, int32_t* local_idx, const Ws& w,
                const Layout& L, hipStream_t stream, int64_t hint_off = 0, bool keep_rule = false) {
-  const bool v4 = aligned16(acc) && ld_acc % 4 == 0 && blocks_vec4(n, P);
   const int32_t smax = (int32_t)L.tiles_tk;
   if (make_hist) {
     SPARDL_TRY(launch_fill(Fill().add(w.hist1, units * L.hcopies * NB1).r, stream));
-    SPARDL_TRY(launch_hist1(acc, ld_acc, units, U, n, P, v4, w.hist1, stream));
+    SPARDL_TRY(launch_hist1(acc, ld_acc, units, U, n, P, w.hist1, stream));
   }
   // the previous-threshold hint feeds the next fused add: kept unless this is a
   // lazy selection that did not start from a fused add; hint_off: the words of
   // the workers before the call's rows (hints are kept per absolute worker)
   uint32_t* hint = (U.rel && !spec) ? nullptr : w.spec_t1 + hint_off;
   SPARDL_TRY(launch_select1(w.hist1, w.state, units, U, n, P, (uint32_t)k_blk, hint, w.spec_used, spec, acc, ld_acc,
-                            v4, w.err, stream));
-  SPARDL_TRY(launch_collect(acc, ld_acc, units, U, n, P, k_blk, v4, smax, w.state, w.spec_cnt, (int32_t)L.add_tiles,
+                            w.err, stream));
+  SPARDL_TRY(launch_collect(acc, ld_acc, units, U, n, P, k_blk, smax, w.state, w.spec_cnt, (int32_t)L.add_tiles,
                             w.slot_cnt, w.slot_nbin, w.cand_idx, w.cand_val, w.bin_key, stream));
   // hist1: the staged threshold for long units builds its level-2/3 histograms in the units'
   // level-1 histogram space, which the select has cleared
@@ -502,8 +502,8 @@ int spardl_residual_add_collect(float* acc, int64_t ld_acc, const float* grad, i
   sp.spec_cnt = w.spec_cnt;
   sp.cand_idx = w.cand_idx;
   sp.cand_val = w.cand_val;
-  if (!v4 || l > COLLECT_MAX_STEPS) {
-    // rows the float4 add does not take: the separate collection of these rows, then the add
+  if (l > COLLECT_MAX_STEPS) {
+    // more SRS steps than the add's collection takes: the separate collection of these rows, then the add
     SPARDL_TRY(launch_grc_zero(acc, ld_acc, nworkers, P, n, k_blk, local_idx, member, stream));
     for (int32_t i = 1; i <= l; ++i) {
       const int32_t m = bag_of(P, l, i);
@@ -533,7 +533,7 @@ int spardl_residual_collect_index(int32_t w0, int32_t nworkers, int64_t n, int32
   const size_t need = spardl_workspace_bytes(1, P, n, k_blk);
   if (need == 0) return SPARDL_EINVAL;
   if (ws_bytes < need) return SPARDL_ECAPACITY;
-  if (l == 0 || l > COLLECT_MAX_STEPS || !blocks_vec4(n, P)) return SPARDL_OK;   // the add collects without an index
+  if (l == 0 || l > COLLECT_MAX_STEPS) return SPARDL_OK;   // the add collects without an index
   const Layout L = make_layout(P, n, k_blk);
   Ws w = carve(ws, ws_bytes, L);
   std::vector<const float*> no_val(l, nullptr);

@@ -35,6 +35,36 @@ __device__ __forceinline__ T early_load(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A row's float4 from element x on, at any dword address.  One that would run
+// past the row's end is loaded from the row's last one (quad_at) and shifted
+// down once it has arrived (quad_shift): elements past the end are unspecified.
+__device__ __forceinline__ uint32_t quad_at(uint32_t x, uint32_t n) { return min(x, n - 4u); }
+__device__ __forceinline__ void quad_shift(f4v& v, uint32_t d) {   // d = x - quad_at(x, n)
+  v.x = d == 0u ? v.x : d == 1u ? v.y : d == 2u ? v.z : v.w;
+  v.y = d == 0u ? v.y : d == 1u ? v.z : v.w;
+  v.z = d == 0u ? v.z : v.w;
+}
+
+// Bit c set: element x + c lies in [s, e).
+__device__ __forceinline__ uint32_t quad_mask(uint32_t x, uint32_t s, uint32_t e) {
+  const uint32_t lo = s > x ? min(s - x, 4u) : 0u, hi = e > x ? min(e - x, 4u) : 0u;
+  return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+}
+
+// The float4's elements inside the block (mask `in`, not 0).
+template <bool RAG>
+__device__ __forceinline__ void store_quad(float* __restrict__ p, f4v q, uint32_t in) {
+  if constexpr (!RAG) {
+    __builtin_nontemporal_store(q, reinterpret_cast<f4v*>(p));
+  } else if (in == 15u) {
+    __builtin_nontemporal_store((f4u)q, reinterpret_cast<f4u*>(p));
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if ((in >> c) & 1u) p[c] = q[c];
+  }
+}
+
 // ============================================================================ a1: residual add
 // Tiles of ADD_TILE elements start at the block's aligned origin (its start
 // rounded down to 32 elements), so every tile after a block's first begins on
@@ -76,14 +106,29 @@ __device__ __forceinline__ T early_load(const T* p) {
 // The separate collection's scattered writes leave a partly written line in
 // the caches for every index they touch, which the next add's stream then
 // writes back; here every line of acc is written once, whole.
+//
+// ROWS_RAGGED takes any block bounds and any 4-byte-aligned rows: gfx950
+// loads and stores 16 bytes at any dword address, and only a block's first
+// and last float4 hold elements outside it (a mask of four bits per float4
+// says which; those are neither counted nor stored).  ROWS_EVEN (every block
+// start, row stride and base a multiple of 16 bytes): a float4 lies wholly
+// inside or outside the block and the masks cost nothing.  ROWS_SHORT: rows
+// of fewer than four elements, which no float4 load fits in.  A worker count
+// or a length that leaves ragged blocks thus keeps the candidates and the
+// fused collection: a step of P = 14 workers with n = 20,033,001 took 1224 us
+// when such rows had a scalar add without candidates and a second read of
+// every block, and 917 us this way; with P = 6, n = 14,715,999 and 10 %
+// density 857 and 765 us.
+enum RowKind : int { ROWS_EVEN, ROWS_RAGGED, ROWS_SHORT };
 constexpr int ADD_STAGE = 512;          // speculative candidates (or drops) staged in LDS per tile
 
-template <bool HIST, bool COLL>
+template <bool HIST, bool COLL, int ROWS>
 __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, int64_t ld_acc,
                                                        const float* __restrict__ grad, int64_t ld_grad, Blocks B,
                                                        uint32_t G, AddSpec sp, AddCollect C) {
   static_assert(ADD_TILE == 2 * 1024, "two 1024-element chunks per tile");
   static_assert(!COLL || HIST, "the fused collection runs in the fused add");
+  constexpr bool RAG = ROWS != ROWS_EVEN;
   __shared__ __align__(16) uint32_t h[HIST ? NB1 : 4];
   __shared__ int32_t s_idx[HIST ? ADD_STAGE : 1];
   __shared__ float s_val[HIST ? ADD_STAGE : 1];
@@ -153,18 +198,32 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   }
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
-  // block starts and ends are multiples of 4 here, so a float4 lies wholly
-  // inside or outside the block; one outside loads the block's first float4
-  // instead (unused), so that the loads need no branch
-  bool in[2];
+  // a float4 outside the block loads the block's first one instead (unused),
+  // so that the loads need no branch
+  uint32_t in[2];   // which of the float4's elements lie in the block
   f4v a[2], gg[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const uint32_t x = x0 + 1024u * j;
-    in[j] = x >= s && x < e;
+    in[j] = RAG ? quad_mask(x, s, e) : x >= s && x < e ? 15u : 0u;
     const uint32_t xl = in[j] ? x : s;
-    a[j] = *reinterpret_cast<const f4v*>(A + xl);
-    gg[j] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(Gr + xl));
+    if constexpr (ROWS == ROWS_SHORT) {
+      a[j] = f4v{0.f, 0.f, 0.f, 0.f};
+      gg[j] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if ((in[j] >> c) & 1u) {
+          a[j][c] = A[x + c];
+          gg[j][c] = Gr[x + c];
+        }
+      }
+    } else if constexpr (RAG) {
+      a[j] = *reinterpret_cast<const f4u*>(A + quad_at(xl, B.n));
+      gg[j] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(Gr + quad_at(xl, B.n)));
+    } else {
+      a[j] = *reinterpret_cast<const f4v*>(A + xl);
+      gg[j] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(Gr + xl));
+    }
   }
   // COLL: the final-index bitmap words of this thread's two float4 (the four
   // elements share a word: tiles start on 32-element boundaries)
@@ -182,7 +241,21 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
     k_need = kp[KEEP_NEEDEQ];
     k_cut = kp[KEEP_CUT];
   }
+  // the row's last float4, where its end is ragged
+  auto shift_ends = [&] {
+    if constexpr (ROWS == ROWS_RAGGED) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint32_t x = x0 + 1024u * j;
+        if (in[j] != 0u && x > B.n - 4u) {
+          quad_shift(a[j], x - (B.n - 4u));
+          quad_shift(gg[j], x - (B.n - 4u));
+        }
+      }
+    }
+  };
   if (!HIST) {
+    shift_ends();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       if (in[j]) {
@@ -191,7 +264,7 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
         q.y = a[j].y + gg[j].y;
         q.z = a[j].z + gg[j].z;
         q.w = a[j].w + gg[j].w;
-        __builtin_nontemporal_store(q, reinterpret_cast<f4v*>(A + x0 + 1024u * j));
+        store_quad<RAG>(A + x0 + 1024u * j, q, in[j]);
       }
     }
     return;
@@ -244,6 +317,7 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
     }
   }
   __syncthreads();
+  shift_ends();
   if constexpr (COLL) {
     // the worker's selections of this block that became final -> 0
     const uint32_t tge = k_tge, teq = k_teq, need_eq = k_need, xcut = k_cut;
@@ -314,13 +388,14 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
       q.y = a[j].y + gg[j].y;
       q.z = a[j].z + gg[j].z;
       q.w = a[j].w + gg[j].w;
-      __builtin_nontemporal_store(q, reinterpret_cast<f4v*>(A + x0 + 1024u * j));
+      store_quad<RAG>(A + x0 + 1024u * j, q, in[j]);
       r[4 * j + 0] = q.x;
       r[4 * j + 1] = q.y;
       r[4 * j + 2] = q.z;
       r[4 * j + 3] = q.w;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
+        if (RAG && !((in[j] >> c) & 1u)) continue;
         const uint32_t key = mag_key(r[4 * j + c]);
         if (key >= FH) atomicAdd(&h[M.bin(key)], 1u);
         packed += key >= F ? (1u << (16 * j)) : 0u;
@@ -360,7 +435,7 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
       uint32_t pos = j == 0 ? (ex & 0xFFFFu) : tot0 + (ex >> 16);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        if (in[j] && mag_key(r[4 * j + c]) >= F) {
+        if ((RAG ? ((in[j] >> c) & 1u) != 0u : in[j] != 0u) && mag_key(r[4 * j + c]) >= F) {
           oI[pos] = (int32_t)(x0 + 1024u * j + (uint32_t)c);
           oV[pos] = r[4 * j + c];
           ++pos;
@@ -381,44 +456,7 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   }
 }
 
-// Rows that are not float4-aligned: one element per thread and step, ADD_F4 * 4
-// steps per tile (tiles from the block start); histogram only, no candidates.
-template <bool HIST>
-__global__ __launch_bounds__(256) void k_residual_add1(float* __restrict__ acc, int64_t ld_acc,
-                                                       const float* __restrict__ grad, int64_t ld_grad, Blocks B,
-                                                       uint32_t G, AddSpec sp) {
-  __shared__ __align__(16) uint32_t h[HIST ? NB1 : 4];
-  const uint32_t g = blockIdx.x % G;
-  const uint32_t wb = blockIdx.x / G;
-  const uint32_t b = wb % B.P, w = wb / B.P;
-  const uint32_t s = B.start(b), e = B.start(b + 1u);
-  const uint32_t t0 = s + g * (uint32_t)ADD_TILE;
-  if (t0 >= e) return;
-  if (HIST) {
-    for (int i = threadIdx.x; i < NB1 / 4; i += 256) reinterpret_cast<uint4*>(h)[i] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-  }
-  float* __restrict__ A = acc + (int64_t)w * ld_acc;
-  const float* __restrict__ Gr = grad + (int64_t)w * ld_grad;
-#pragma unroll
-  for (int j = 0; j < ADD_F4 * 4; ++j) {
-    const uint32_t off = t0 + j * 256u + threadIdx.x;
-    if (off < e) {
-      const float r = A[off] + Gr[off];
-      A[off] = r;
-      if (HIST) atomicAdd(&h[mag_key(r) >> D1_SHIFT], 1u);
-    }
-  }
-  if (HIST) {
-    if (g == 0u && threadIdx.x == 0) sp.spec_used[wb] = SPEC_NONE;   // no candidates on this path
-    __syncthreads();
-    uint32_t* __restrict__ H = sp.hist1 + ((int64_t)wb * sp.hcopies + blockIdx.x % HCOPIES_MIN) * NB1;
-    flush_hist<256>(h, H);
-  }
-}
-
 // Level-1 histogram only (block_topk without a fused residual add).
-template <int VEC>
 __global__ __launch_bounds__(256) void k_hist1(const float* __restrict__ acc, int64_t ld_acc, Blocks B, Units U,
                                                uint32_t G, uint32_t hc, uint32_t* __restrict__ hist1) {
   __shared__ __align__(16) uint32_t h[NB1];
@@ -432,23 +470,17 @@ __global__ __launch_bounds__(256) void k_hist1(const float* __restrict__ acc, in
   for (int i = threadIdx.x; i < NB1 / 4; i += 256) reinterpret_cast<uint4*>(h)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
   const float* __restrict__ A = acc + (int64_t)w * ld_acc;
-  if (VEC == 4) {
 #pragma unroll
-    for (int j = 0; j < ADD_F4; ++j) {
-      const uint32_t off = t0 + (j * 256u + threadIdx.x) * 4u;
-      if (off < e) {
-        const f4v a = *reinterpret_cast<const f4v*>(A + off);
-        atomicAdd(&h[mag_key(a.x) >> D1_SHIFT], 1u);
-        atomicAdd(&h[mag_key(a.y) >> D1_SHIFT], 1u);
-        atomicAdd(&h[mag_key(a.z) >> D1_SHIFT], 1u);
-        atomicAdd(&h[mag_key(a.w) >> D1_SHIFT], 1u);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < ADD_F4 * 4; ++j) {
-      const uint32_t off = t0 + j * 256u + threadIdx.x;
-      if (off < e) atomicAdd(&h[mag_key(A[off]) >> D1_SHIFT], 1u);
+  for (int j = 0; j < ADD_F4; ++j) {
+    const uint32_t off = t0 + (j * 256u + threadIdx.x) * 4u;
+    if (off < e && e - off >= 4u) {
+      const f4v a = *reinterpret_cast<const f4u*>(A + off);
+      atomicAdd(&h[mag_key(a.x) >> D1_SHIFT], 1u);
+      atomicAdd(&h[mag_key(a.y) >> D1_SHIFT], 1u);
+      atomicAdd(&h[mag_key(a.z) >> D1_SHIFT], 1u);
+      atomicAdd(&h[mag_key(a.w) >> D1_SHIFT], 1u);
+    } else {   // the block's last elements
+      for (uint32_t x = off; x < e; ++x) atomicAdd(&h[mag_key(A[x]) >> D1_SHIFT], 1u);
     }
   }
   __syncthreads();
@@ -471,38 +503,40 @@ hipError_t launch_residual_add(float* acc, int64_t ld_acc, const float* grad, in
   const bool hist = sp.hist1 != nullptr;
   AddSpec spc = sp;
   spc.hcopies = hist_copies_for(n, P);
-  if (C.member && !(hist && vec4)) return hipErrorInvalidValue;   // the fused collection needs the fused float4 add
+  if (C.member && !hist) return hipErrorInvalidValue;   // the fused collection needs the fused add
   const int32_t PP = hist ? P : 1;
   const int64_t maxlen = (n + PP - 1) / PP;
   const Blocks B = make_blocks(n, PP);
-  if (vec4) {
-    // tiles from each block's aligned origin: up to 31 more elements per block
-    const uint32_t G = (uint32_t)add_tiles_per_block(maxlen);
-    const dim3 grid(G, (unsigned)PP, (unsigned)nworkers);
-    if (C.member)
-      hipLaunchKernelGGL((k_residual_add4<true, true>), grid, dim3(256), 0, s, acc, ld_acc, grad, ld_grad, B, G, spc, C);
-    else if (hist)
-      hipLaunchKernelGGL((k_residual_add4<true, false>), grid, dim3(256), 0, s, acc, ld_acc, grad, ld_grad, B, G, spc, C);
-    else
-      hipLaunchKernelGGL((k_residual_add4<false, false>), grid, dim3(256), 0, s, acc, ld_acc, grad, ld_grad, B, G, spc, C);
-  } else {
-    const uint32_t G = (uint32_t)((maxlen + ADD_TILE - 1) / ADD_TILE);
-    const dim3 grid((unsigned)((int64_t)nworkers * PP * G));
-    if (hist) hipLaunchKernelGGL(k_residual_add1<true>, grid, dim3(256), 0, s, acc, ld_acc, grad, ld_grad, B, G, spc);
-    else hipLaunchKernelGGL(k_residual_add1<false>, grid, dim3(256), 0, s, acc, ld_acc, grad, ld_grad, B, G, sp);
-  }
+  // tiles from each block's aligned origin: up to 31 more elements per block
+  const uint32_t G = (uint32_t)add_tiles_per_block(maxlen);
+  auto go = [&](auto kernel) {
+    // at most 65535 rows per launch (with HIST there are at most P rows, and a workspace holds far fewer)
+    constexpr int32_t ROWS = 65535;
+    for (int32_t w = 0; w < nworkers; w += ROWS)
+      hipLaunchKernelGGL(kernel, dim3(G, (unsigned)PP, (unsigned)std::min(nworkers - w, ROWS)), dim3(256), 0, s,
+                         acc + w * ld_acc, ld_acc, grad + w * ld_grad, ld_grad, B, G, spc, C);
+  };
+  auto pick = [&](auto even, auto ragged, auto brief) { vec4 ? go(even) : n >= 4 ? go(ragged) : go(brief); };
+  if (C.member)
+    pick(k_residual_add4<true, true, ROWS_EVEN>, k_residual_add4<true, true, ROWS_RAGGED>,
+         k_residual_add4<true, true, ROWS_SHORT>);
+  else if (hist)
+    pick(k_residual_add4<true, false, ROWS_EVEN>, k_residual_add4<true, false, ROWS_RAGGED>,
+         k_residual_add4<true, false, ROWS_SHORT>);
+  else
+    pick(k_residual_add4<false, false, ROWS_EVEN>, k_residual_add4<false, false, ROWS_RAGGED>,
+         k_residual_add4<false, false, ROWS_SHORT>);
   return hipGetLastError();
 }
 
 hipError_t launch_hist1(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
-                        bool vec4, uint32_t* hist1, hipStream_t s) {
+                        uint32_t* hist1, hipStream_t s) {
   const int64_t maxlen = (n + P - 1) / P;
   const int32_t G = (int32_t)((maxlen + ADD_TILE - 1) / ADD_TILE);
   const dim3 grid((unsigned)(nunits * G));
   const Blocks B = make_blocks(n, P);
   const uint32_t hc = hist_copies_for(n, P);
-  if (vec4) hipLaunchKernelGGL(k_hist1<4>, grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)G, hc, hist1);
-  else hipLaunchKernelGGL(k_hist1<1>, grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)G, hc, hist1);
+  hipLaunchKernelGGL(k_hist1, grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)G, hc, hist1);
   return hipGetLastError();
 }
 

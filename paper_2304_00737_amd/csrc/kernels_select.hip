@@ -32,7 +32,7 @@ namespace spardl {
 __global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, uint32_t* __restrict__ state,
                                                   Blocks B, Units U, uint32_t need, uint32_t* __restrict__ spec_t1,
                                                   const uint32_t* __restrict__ spec_used, int spec,
-                                                  const float* __restrict__ acc, int64_t ld_acc, int vec4,
+                                                  const float* __restrict__ acc, int64_t ld_acc,
                                                   uint32_t hc, uint32_t* __restrict__ err) {
   constexpr int NT = 1024, PER = NB1 / NT;
   static_assert(HCOPIES_MIN == 4, "copies are summed four at a time");
@@ -75,27 +75,25 @@ __global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, 
     for (int i = threadIdx.x; i < NB1; i += NT) h[i] = 0u;
     __syncthreads();
     const float* __restrict__ A = acc + (int64_t)w * ld_acc;
-    if (vec4) {
-      for (uint32_t x0 = s + threadIdx.x * 4u; x0 < e; x0 += NT * 4u * 4u) {
-        f4v v[4];
+    for (uint32_t x0 = s + threadIdx.x * 4u; x0 < e; x0 += NT * 4u * 4u) {
+      f4v v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t x = x0 + (uint32_t)k * NT * 4u;
-          if (x < e) v[k] = *reinterpret_cast<const f4v*>(A + x);
-        }
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t x = x0 + (uint32_t)k * NT * 4u;
+        if (x < e && e - x >= 4u) v[k] = *reinterpret_cast<const f4u*>(A + x);
+      }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t x = x0 + (uint32_t)k * NT * 4u;
-          if (x < e) {
-            atomicAdd(&h[mag_key(v[k].x) >> D1_SHIFT], 1u);
-            atomicAdd(&h[mag_key(v[k].y) >> D1_SHIFT], 1u);
-            atomicAdd(&h[mag_key(v[k].z) >> D1_SHIFT], 1u);
-            atomicAdd(&h[mag_key(v[k].w) >> D1_SHIFT], 1u);
-          }
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t x = x0 + (uint32_t)k * NT * 4u;
+        if (x < e && e - x >= 4u) {
+          atomicAdd(&h[mag_key(v[k].x) >> D1_SHIFT], 1u);
+          atomicAdd(&h[mag_key(v[k].y) >> D1_SHIFT], 1u);
+          atomicAdd(&h[mag_key(v[k].z) >> D1_SHIFT], 1u);
+          atomicAdd(&h[mag_key(v[k].w) >> D1_SHIFT], 1u);
+        } else if (x < e) {   // the block's last elements
+          for (uint32_t y = x; y < e; ++y) atomicAdd(&h[mag_key(A[y]) >> D1_SHIFT], 1u);
         }
       }
-    } else {
-      for (uint32_t x = s + threadIdx.x; x < e; x += NT) atomicAdd(&h[mag_key(A[x]) >> D1_SHIFT], 1u);
     }
     __syncthreads();
     block_select_desc(h, NB1, need, scratch, &T, &above, &cnt, &ok, &total);
@@ -186,7 +184,7 @@ struct CollectSmem {
   uint32_t cb[SLOT / 256 * 4 + 1];   // ... and threshold-bin entries
 };
 
-template <int VEC, bool FULL>
+template <bool FULL>
 __device__ __forceinline__ void collect_slot(const float* __restrict__ A, uint32_t nvalid, int32_t pos0,
                                              const uint32_t* __restrict__ st, CollectSmem& L,
                                              uint32_t* cnt_out, uint32_t* nbin_out, int32_t* __restrict__ CI,
@@ -195,19 +193,21 @@ __device__ __forceinline__ void collect_slot(const float* __restrict__ A, uint32
   const int lane = lane_id(), wv = wave_id();
   const uint32_t my0 = threadIdx.x * PT;
   float v[PT];
-  if (VEC == 4) {
 #pragma unroll
-    for (int q = 0; q < PT / 4; ++q) {
-      f4v x = {0.f, 0.f, 0.f, 0.f};
-      if (FULL || my0 + 4 * q < nvalid) x = *reinterpret_cast<const f4v*>(A + my0 + 4 * q);
-      v[4 * q + 0] = x.x;
-      v[4 * q + 1] = x.y;
-      v[4 * q + 2] = x.z;
-      v[4 * q + 3] = x.w;
+  for (int q = 0; q < PT / 4; ++q) {
+    const uint32_t o = my0 + 4 * q;
+    f4v x = {0.f, 0.f, 0.f, 0.f};
+    if (FULL || o + 3u < nvalid) {
+      x = *reinterpret_cast<const f4u*>(A + o);
+    } else if (o < nvalid) {   // the block's last elements
+      x.x = A[o];
+      if (o + 1u < nvalid) x.y = A[o + 1u];
+      if (o + 2u < nvalid) x.z = A[o + 2u];
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < PT; ++i) v[i] = (FULL || my0 + i < nvalid) ? A[my0 + i] : 0.f;
+    v[4 * q + 0] = x.x;
+    v[4 * q + 1] = x.y;
+    v[4 * q + 2] = x.z;
+    v[4 * q + 3] = x.w;
   }
   // the threshold bin is read only now, so its latency overlaps the data loads
   __builtin_amdgcn_sched_barrier(0);
@@ -394,7 +394,7 @@ static inline int topk_slots_per_wave(int64_t nunits, int32_t smax, int32_t kb) 
   if (nunits * smax < MULTI_SLOT_MIN) return 1;
   return (int64_t)kb < 8ll * smax ? 8 : 2;
 }
-template <int VEC, int SPW>
+template <int SPW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPW >= 8 ? 5 : 8, 8))) void k_collect(const float* __restrict__ acc, int64_t ld_acc, Blocks B, Units U,
                                                  uint32_t smax, uint32_t gq, const uint32_t* __restrict__ state,
                                                  const uint32_t* __restrict__ spec_cnt, uint32_t add_tiles,
@@ -508,10 +508,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPW >= 8 ? 
     const int64_t cbase = (int64_t)w * B.n + t0;
     const int64_t si = (int64_t)unit * smax + slot;
     if (nvalid == (uint32_t)SLOT)
-      collect_slot<VEC, true>(A, nvalid, (int32_t)t0, st, L, slot_cnt + si, slot_nbin + si,
+      collect_slot<true>(A, nvalid, (int32_t)t0, st, L, slot_cnt + si, slot_nbin + si,
                               cand_idx + cbase, cand_val + cbase, bin_key + cbase);
     else
-      collect_slot<VEC, false>(A, nvalid, (int32_t)t0, st, L, slot_cnt + si, slot_nbin + si,
+      collect_slot<false>(A, nvalid, (int32_t)t0, st, L, slot_cnt + si, slot_nbin + si,
                                cand_idx + cbase, cand_val + cbase, bin_key + cbase);
   }
 }
@@ -1758,25 +1758,23 @@ __global__ __launch_bounds__(256) void k_emit(
 // ============================================================================ launchers
 hipError_t launch_select1(uint32_t* hist1, uint32_t* state, int64_t nunits, const Units& U, int64_t n, int32_t P,
                           uint32_t need, uint32_t* spec_t1, const uint32_t* spec_used, bool spec, const float* acc,
-                          int64_t ld_acc, bool vec4, uint32_t* err, hipStream_t s) {
+                          int64_t ld_acc, uint32_t* err, hipStream_t s) {
   hipLaunchKernelGGL(k_select1, dim3((unsigned)nunits), dim3(1024), 0, s, hist1, state, make_blocks(n, P), U, need,
-                     spec_t1, spec_used, spec ? 1 : 0, acc, ld_acc, vec4 ? 1 : 0, hist_copies_for(n, P), err);
+                     spec_t1, spec_used, spec ? 1 : 0, acc, ld_acc, hist_copies_for(n, P), err);
   return hipGetLastError();
 }
 
 hipError_t launch_collect(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
-                          int32_t kb, bool vec4, int32_t smax, const uint32_t* state, const uint32_t* spec_cnt,
+                          int32_t kb, int32_t smax, const uint32_t* state, const uint32_t* spec_cnt,
                           int32_t add_tiles, uint32_t* slot_cnt, uint32_t* slot_nbin, int32_t* cand_idx,
                           float* cand_val, uint32_t* bin_key, hipStream_t s) {
-  // the speculative path exists for float4 rows only (the add writes no candidates otherwise)
-  const int spw = vec4 ? topk_slots_per_wave(nunits, smax, kb) : 1;
+  const int spw = topk_slots_per_wave(nunits, smax, kb);
   const uint32_t gq = (uint32_t)((smax + 4 * spw - 1) / (4 * spw));
   const dim3 grid((unsigned)(nunits * gq));
   const Blocks B = make_blocks(n, P);
-  if (spw == 8) hipLaunchKernelGGL((k_collect<4, 8>), grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)smax, gq, state, spec_cnt, (uint32_t)add_tiles, slot_cnt, slot_nbin, cand_idx, cand_val, bin_key);
-  else if (spw == 2) hipLaunchKernelGGL((k_collect<4, 2>), grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)smax, gq, state, spec_cnt, (uint32_t)add_tiles, slot_cnt, slot_nbin, cand_idx, cand_val, bin_key);
-  else if (vec4) hipLaunchKernelGGL((k_collect<4, 1>), grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)smax, gq, state, spec_cnt, (uint32_t)add_tiles, slot_cnt, slot_nbin, cand_idx, cand_val, bin_key);
-  else hipLaunchKernelGGL((k_collect<1, 1>), grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)smax, gq, state, spec_cnt, (uint32_t)add_tiles, slot_cnt, slot_nbin, cand_idx, cand_val, bin_key);
+  if (spw == 8) hipLaunchKernelGGL(k_collect<8>, grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)smax, gq, state, spec_cnt, (uint32_t)add_tiles, slot_cnt, slot_nbin, cand_idx, cand_val, bin_key);
+  else if (spw == 2) hipLaunchKernelGGL(k_collect<2>, grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)smax, gq, state, spec_cnt, (uint32_t)add_tiles, slot_cnt, slot_nbin, cand_idx, cand_val, bin_key);
+  else hipLaunchKernelGGL(k_collect<1>, grid, dim3(256), 0, s, acc, ld_acc, B, U, (uint32_t)smax, gq, state, spec_cnt, (uint32_t)add_tiles, slot_cnt, slot_nbin, cand_idx, cand_val, bin_key);
   return hipGetLastError();
 }
 

@@ -1,0 +1,68 @@
+"""Ragged rows and blocks through the float4 residual add: block bounds, row
+strides and base addresses that are no multiples of a float4, rows shorter
+than one, tiles that end one element past or short of a block; the fused
+add's candidates and collection hold there too.  Bit for bit against the
+oracle (every value has one IEEE sum, so there is no tolerance)."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import spardl_oracle as so
+from paper_2304_00737_amd import workloads as W
+from tests.gpu_util import assert_bits_equal, check_ws, compare_step, log, ws_spec_ok
+
+pytestmark = pytest.mark.gpu
+spardl = pytest.importorskip("paper_2304_00737_amd.spardl")
+
+# rows shorter than a float4, of one, of a few; blocks a tile (2048) long and one
+# element more or less; 14 and 6 workers with lengths no block size divides
+SIZES = [(1, 1, 1), (2, 3, 1), (3, 3, 1), (1, 4, 2), (2, 5, 1), (3, 7, 2), (2, 9, 4), (5, 67, 3),
+         (2, 4094, 20), (2, 4097, 20), (3, 6145, 33), (3, 12287, 100), (6, 40001, 70), (14, 100003, 71)]
+
+
+@pytest.mark.parametrize("collect", ["fused", "separate", "plain"])
+@pytest.mark.parametrize("P,n,kb", SIZES)
+def test_ragged_steps(P, n, kb, collect):
+    log(f"ragged step P={P} n={n} kb={kb} {collect}")
+    st = spardl.SparDLStep(P, n, kb, fused=collect != "plain", fuse_collect=collect == "fused")
+    acc = np.zeros((P, n), np.float32)
+    for t in range(4):
+        grad = W.small_rows("normal" if t != 2 else "ties", P, n, 31 * t + n)
+        st.step(torch.from_numpy(grad).cuda())
+        check_ws(st)
+        res = so.spardl_step([acc[w] for w in range(P)], [grad[w] for w in range(P)], P, n, kb)
+        compare_step(st, res, P, n, kb, residual=collect != "fused")
+    if collect == "fused" and n > 4096:
+        st.step(torch.from_numpy(W.small_rows("normal", P, n, 7)).cuda())
+        st.step(torch.from_numpy(W.small_rows("normal", P, n, 8)).cuda())
+        assert all(ws_spec_ok(st)), "ragged blocks keep the speculative candidates"
+
+
+@pytest.mark.parametrize("off_a,off_g,pad", [(0, 1, 0), (1, 0, 1), (2, 3, 2), (3, 3, 31), (0, 0, 3)])
+@pytest.mark.parametrize("P,n", [(3, 5), (4, 8192), (5, 9001)])
+def test_add_any_address(P, n, off_a, off_g, pad):
+    """Rows at any 4-byte address and any stride, with and without the fused
+    histogram: nothing outside the rows is written."""
+    log(f"add any address P={P} n={n} acc+{off_a} grad+{off_g} ld=n+{pad}")
+    ld = n + pad
+    for ws in (None, spardl.workspace(P, P, n, 1)):
+        a = np.random.default_rng(n + pad).standard_normal(P * ld + 8).astype(np.float32)
+        g = np.random.default_rng(n + 1).standard_normal(P * ld + 8).astype(np.float32)
+        at, gt = torch.from_numpy(a).cuda(), torch.from_numpy(g).cuda()
+        spardl.residual_add(at.data_ptr() + 4 * off_a, gt.data_ptr() + 4 * off_g, P, n, P if ws is not None else 0,
+                            ws, 1, ld_acc=ld, ld_grad=ld)
+        want = a.copy()
+        for w in range(P):
+            s, q = off_a + w * ld, off_g + w * ld
+            want[s:s + n] = so.residual_add(a[s:s + n], g[q:q + n])
+        assert_bits_equal(at.cpu().numpy(), want, "rows and what surrounds them")
+
+
+def test_plain_add_many_rows():
+    """More rows than one launch's grid holds."""
+    log("plain add of 70000 rows of 3")
+    a, g = torch.randn(70000, 3, device="cuda"), torch.randn(70000, 3, device="cuda")
+    want = a + g
+    spardl.residual_add(a, g, 70000, 3)
+    assert torch.equal(a, want)
