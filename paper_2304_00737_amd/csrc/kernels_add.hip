@@ -72,9 +72,14 @@ __device__ __forceinline__ void store_quad(float* __restrict__ p, f4v q, uint32_
 // [origin + g ADD_TILE, origin + (g+1) ADD_TILE) clipped to the block.
 // One workgroup per tile; chunk j of the tile is the 1024 elements at
 // 1024 j, thread t holding elements 4t .. 4t+3 of each chunk, so each wave's
-// float4 access covers 1 KB of whole lines.  The gradient is read once, so it
-// is loaded non-temporally; A is re-read only by a fallback, so it is stored
-// non-temporally.
+// float4 access covers 1 KB of whole lines.  Nothing of the stream is used
+// again before the whole of it has passed, so all of it is non-temporal: the
+// gradient's loads, A's stores (a fallback alone reads A again) and A's loads.
+// Loading A through the caches' normal policy instead cost most of what bound
+// this kernel: 456 against 412 us for 8 rows of 25.6M (2.46 GB), 4355 against
+// 3643 us for 16 of 110M, 3415 against 2981 us for one of 1.5G (6.0 TB/s);
+// rows that fit the 256 MB cache take the same time either way (8 of 1M to
+// 8M).
 //
 // With HIST, every sum's level-1 bin (L1Map in device.hpp) is counted in an
 // LDS histogram that is flushed (non-zero bins only) into one of the block's
@@ -218,10 +223,10 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
         }
       }
     } else if constexpr (RAG) {
-      a[j] = *reinterpret_cast<const f4u*>(A + quad_at(xl, B.n));
+      a[j] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(A + quad_at(xl, B.n)));
       gg[j] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(Gr + quad_at(xl, B.n)));
     } else {
-      a[j] = *reinterpret_cast<const f4v*>(A + xl);
+      a[j] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(A + xl));
       gg[j] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(Gr + xl));
     }
   }
