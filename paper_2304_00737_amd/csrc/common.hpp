@@ -22,8 +22,7 @@ constexpr int NB3 = 256;
 // dispatched in address order (this keeps DRAM pages open and beats both
 // larger per-lane batches and workgroups that walk long ranges).
 constexpr int WAVE = 64;
-constexpr int ADD_F4 = 2;                        // float4 per lane per array in the residual add
-constexpr int ADD_TILE = 256 * ADD_F4 * 4;       // elements per residual-add workgroup
+constexpr int ADD_TILE = 2048;                   // elements per residual-add workgroup
 constexpr int SLOT = 4096;                       // elements per candidate slot (one collect workgroup)
 constexpr int MERGE_THREADS = 1024;               // a merge tile's serial steps (split search, merge,
 constexpr int MERGE_PER_THREAD = 4;                // histogram flush, bin sort) shrink with the positions per thread
@@ -104,9 +103,15 @@ __host__ __device__ __forceinline__ int64_t blk_start(int64_t b, int64_t n, int6
 // host, start(b) = b q + floor(b r / P) takes 32-bit arithmetic only when
 // P < 2^16 (b r < P^2 < 2^32); kernels index everything in 32 bits so that no
 // 64-bit division (a long scalar sequence per wave) precedes their loads.
+// For P <= START_MUL_MAX the quotient floor(x / P) of x = b r < P^2 is the high
+// word of x inv with inv = floor(2^32 / P) + 1: inv P exceeds 2^32 by at most
+// P, so the product exceeds 2^32 (x / P) by at most x < 2^32 / P (a division
+// is some 25 vector instructions, in every wave).
+constexpr uint32_t START_MUL_MAX = 1024;
 struct Blocks {
-  uint32_t n, P, q, r;
+  uint32_t n, P, q, r, inv;
   __device__ __forceinline__ uint32_t start(uint32_t b) const {
+    if (inv) return b * q + __umulhi(b * r, inv);
     if (P < 65536u) return b * q + (b * r) / P;
     return (uint32_t)(((uint64_t)b * n) / P);
   }
@@ -121,7 +126,9 @@ struct Blocks {
 };
 
 inline Blocks make_blocks(int64_t n, int32_t P) {
-  return Blocks{(uint32_t)n, (uint32_t)P, (uint32_t)(n / P), (uint32_t)(n % P)};
+  // (P = 1: r = 0, any multiplier)
+  const uint32_t inv = (uint32_t)P > START_MUL_MAX ? 0u : P == 1 ? 1u : (uint32_t)((1ull << 32) / (uint64_t)P) + 1u;
+  return Blocks{(uint32_t)n, (uint32_t)P, (uint32_t)(n / P), (uint32_t)(n % P), inv};
 }
 
 // Tiles of the fused residual add and slots of the block top-k start at a

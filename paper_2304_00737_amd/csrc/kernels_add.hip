@@ -70,9 +70,9 @@ __device__ __forceinline__ void store_quad(float* __restrict__ p, f4v q, uint32_
 // rounded down to 32 elements), so every tile after a block's first begins on
 // a 128-byte boundary of the row; tile g of block b is
 // [origin + g ADD_TILE, origin + (g+1) ADD_TILE) clipped to the block.
-// One workgroup per tile; chunk j of the tile is the 1024 elements at
-// 1024 j, thread t holding elements 4t .. 4t+3 of each chunk, so each wave's
-// float4 access covers 1 KB of whole lines.  Nothing of the stream is used
+// One workgroup per tile; thread t holds elements 4t .. 4t+3 of each chunk of
+// four elements per thread, so each wave's float4 access covers 1 KB of whole
+// lines.  Nothing of the stream is used
 // again before the whole of it has passed, so all of it is non-temporal: the
 // gradient's loads, A's stores (a fallback alone reads A again) and A's loads.
 // Loading A through the caches' normal policy instead cost most of what bound
@@ -127,17 +127,32 @@ __device__ __forceinline__ void store_quad(float* __restrict__ p, f4v q, uint32_
 enum RowKind : int { ROWS_EVEN, ROWS_RAGGED, ROWS_SHORT };
 constexpr int ADD_STAGE = 512;          // speculative candidates (or drops) staged in LDS per tile
 
+//
+// Without COLL a tile has 512 threads of one float4 each: an in-place add on
+// its own streams faster so (0.2G elements 387 against 396 us, 1.76G 3377
+// against 3495 us), and the block's tiles go to the XCDs in eight contiguous
+// runs instead of round-robin, which keeps each XCD in fewer pages.  Against
+// 256 threads of two float4, round-robin: one row of 1.5G 2983 -> 2845
+// (threads) -> 2776 us (order; 6.5 TB/s), 8 rows of 25.6M 395 -> 394 -> 381,
+// 6 ragged rows of 14.7M at 10 % 251 -> 251 -> 226.  With COLL the collection's
+// instructions and barriers per wave weigh more than that: 415 us for 8 rows of
+// 25.6M with 256 threads, 483 with 512, and contiguous runs cost 4-8 %.
+constexpr int add_threads(bool coll) { return coll ? 256 : 512; }
+
 template <bool HIST, bool COLL, int ROWS>
-__global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, int64_t ld_acc,
+__global__ __launch_bounds__(add_threads(COLL)) void k_residual_add4(float* __restrict__ acc, int64_t ld_acc,
                                                        const float* __restrict__ grad, int64_t ld_grad, Blocks B,
                                                        uint32_t G, AddSpec sp, AddCollect C) {
-  static_assert(ADD_TILE == 2 * 1024, "two 1024-element chunks per tile");
+  constexpr int NT = add_threads(COLL), NW = NT / WAVE;
+  constexpr int CH = 4 * NT;           // elements the threads cover with one float4 each
+  constexpr int F4 = ADD_TILE / CH;    // float4 per thread and array
+  static_assert(F4 * CH == ADD_TILE && F4 <= 2, "whole float4 per thread; packed counts of two chunks");
   static_assert(!COLL || HIST, "the fused collection runs in the fused add");
   constexpr bool RAG = ROWS != ROWS_EVEN;
   __shared__ __align__(16) uint32_t h[HIST ? NB1 : 4];
   __shared__ int32_t s_idx[HIST ? ADD_STAGE : 1];
   __shared__ float s_val[HIST ? ADD_STAGE : 1];
-  __shared__ uint32_t wtot[4];
+  __shared__ uint32_t wtot[NW];
   // COLL: the tile image (in the histogram's space: each thread clears its
   // words of it again after the collection), the tile's final-index bitmap
   // words, and per SRS step the range of the worker's drops inside the tile
@@ -150,7 +165,8 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   __shared__ const int32_t* c_di[COLL ? COLLECT_MAX_STEPS : 1];
   __shared__ const float* c_dv[COLL ? COLLECT_MAX_STEPS : 1];
   // grid: x = tile of the block, y = block, z = row (no division decodes it)
-  const uint32_t g = blockIdx.x;
+  uint32_t g = blockIdx.x;
+  if (!COLL && g < (G & ~7u)) g = (g & 7u) * (G / 8u) + (g >> 3);   // an eighth of the block per XCD
   const uint32_t b = blockIdx.y, w = blockIdx.z;
   const uint32_t wb = w * B.P + b;
   const uint32_t s = B.start(b), e = B.start(b + 1u);
@@ -167,7 +183,7 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   // relaxed atomic loads behind a compiler-only fence, which the compiler
   // neither sinks below the stream nor waits for at once.
   const uint32_t wa = C.w0 + w;   // COLL: the absolute worker
-  const uint32_t tt = (b + B.P - wa % B.P) % B.P;   // COLL: this block's place in the worker's bags
+  const uint32_t tt = b >= wa ? b - wa : b + B.P - wa;   // COLL: this block's place in the worker's bags
   constexpr int RR_EARLY = 8;
   uint2 rr[RR_EARLY];
   int32_t rc[RR_EARLY];   // COLL: the pair's drop count of each step
@@ -205,11 +221,11 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   __builtin_amdgcn_sched_barrier(0);
   // a float4 outside the block loads the block's first one instead (unused),
   // so that the loads need no branch
-  uint32_t in[2];   // which of the float4's elements lie in the block
-  f4v a[2], gg[2];
+  uint32_t in[F4];   // which of the float4's elements lie in the block
+  f4v a[F4], gg[F4];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const uint32_t x = x0 + 1024u * j;
+  for (int j = 0; j < F4; ++j) {
+    const uint32_t x = x0 + (uint32_t)(CH * j);
     in[j] = RAG ? quad_mask(x, s, e) : x >= s && x < e ? 15u : 0u;
     const uint32_t xl = in[j] ? x : s;
     if constexpr (ROWS == ROWS_SHORT) {
@@ -232,12 +248,12 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   }
   // COLL: the final-index bitmap words of this thread's two float4 (the four
   // elements share a word: tiles start on 32-element boundaries)
-  uint32_t mw[2] = {0u, 0u};
+  uint32_t mw[F4] = {};
   uint32_t k_tge = 0, k_teq = 0, k_need = 0, k_cut = 0;   // COLL: the block top-k's selection rule
   if constexpr (COLL) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t x = x0 + 1024u * j;
+    for (int j = 0; j < F4; ++j) {
+      const uint32_t x = x0 + (uint32_t)(CH * j);
       if (x < B.n) mw[j] = C.member[x >> 5];
     }
     const uint32_t* __restrict__ kp = C.keep + ((int64_t)(C.w0 + w) * B.P + b) * KEEP_WORDS;
@@ -250,8 +266,8 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   auto shift_ends = [&] {
     if constexpr (ROWS == ROWS_RAGGED) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const uint32_t x = x0 + 1024u * j;
+      for (int j = 0; j < F4; ++j) {
+        const uint32_t x = x0 + (uint32_t)(CH * j);
         if (in[j] != 0u && x > B.n - 4u) {
           quad_shift(a[j], x - (B.n - 4u));
           quad_shift(gg[j], x - (B.n - 4u));
@@ -262,21 +278,21 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   if (!HIST) {
     shift_ends();
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < F4; ++j) {
       if (in[j]) {
         f4v q;
         q.x = a[j].x + gg[j].x;
         q.y = a[j].y + gg[j].y;
         q.z = a[j].z + gg[j].z;
         q.w = a[j].w + gg[j].w;
-        store_quad<RAG>(A + x0 + 1024u * j, q, in[j]);
+        store_quad<RAG>(A + x0 + (uint32_t)(CH * j), q, in[j]);
       }
     }
     return;
   }
   // the histogram is cleared while the loads are in flight (with COLL, a tile
   // with drops clears its image's words again after the collection)
-  for (int i = threadIdx.x; i < NB1 / 4; i += 256) reinterpret_cast<uint4*>(h)[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (int i = threadIdx.x; i < NB1 / 4; i += NT) reinterpret_cast<uint4*>(h)[i] = make_uint4(0u, 0u, 0u, 0u);
   uint32_t F = SPEC_NONE;
   sw = max(sw, pw);
   if (sw != 0u) {
@@ -327,11 +343,11 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
     // the worker's selections of this block that became final -> 0
     const uint32_t tge = k_tge, teq = k_teq, need_eq = k_need, xcut = k_cut;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < F4; ++j) {
       if (in[j]) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          const uint32_t x = x0 + 1024u * j + (uint32_t)c;
+          const uint32_t x = x0 + (uint32_t)(CH * j + c);
           const uint32_t key = mag_key(a[j][c]);
           const bool sel = key >= tge || (need_eq != 0u && key == teq && x <= xcut);
           if (sel && ((mw[j] >> (x & 31u)) & 1u)) a[j][c] = 0.0f;
@@ -342,15 +358,15 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
     if (ndrop != 0u) {
       // the final drops of SRS steps 1..l, in order, on the tile image
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        if (in[j]) *reinterpret_cast<f4v*>(cimg + threadIdx.x * 4u + 1024u * j) = a[j];
+      for (int j = 0; j < F4; ++j)
+        if (in[j]) *reinterpret_cast<f4v*>(cimg + threadIdx.x * 4u + (uint32_t)(CH * j)) = a[j];
       if ((threadIdx.x & 7u) == 0u) {
-        cmw[threadIdx.x >> 3] = mw[0];
-        cmw[32u + (threadIdx.x >> 3)] = mw[1];
+#pragma unroll
+        for (int j = 0; j < F4; ++j) cmw[(threadIdx.x >> 3) + (uint32_t)(j * CH / 32)] = mw[j];
       }
       const bool staged = ndrop <= (uint32_t)ADD_STAGE;   // uniform: every step's drops in one round of loads
       if (staged) {
-        for (uint32_t f = threadIdx.x; f < ndrop; f += 256u) {
+        for (uint32_t f = threadIdx.x; f < ndrop; f += NT) {
           int i = 0;
           while (f >= c_cum[i + 1]) ++i;
           const uint32_t jj = c_lo[i] + (f - c_cum[i]);
@@ -362,7 +378,7 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
       for (int i = 0; i < C.l; ++i) {
         const uint32_t lo = c_lo[i], hi = c_hi[i];
         if (hi == lo) continue;   // uniform
-        for (uint32_t jj = lo + threadIdx.x; jj < hi; jj += 256u) {
+        for (uint32_t jj = lo + threadIdx.x; jj < hi; jj += NT) {
           const uint32_t f = c_cum[i] + (jj - lo);
           const int32_t x = staged ? s_idx[f] : c_di[i][jj];
           const float v = staged ? s_val[f] : c_dv[i][jj];
@@ -375,25 +391,25 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
       // each thread reads back its own words of the image and clears them for the
       // histogram; the barrier orders every clear before any histogram update
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        f4v* q = reinterpret_cast<f4v*>(cimg + threadIdx.x * 4u + 1024u * j);
+      for (int j = 0; j < F4; ++j) {
+        f4v* q = reinterpret_cast<f4v*>(cimg + threadIdx.x * 4u + (uint32_t)(CH * j));
         if (in[j]) a[j] = *q;
         *q = f4v{0.f, 0.f, 0.f, 0.f};
       }
       __syncthreads();
     }
   }
-  float r[8];
+  float r[4 * F4];
   uint32_t packed = 0;   // candidates of chunk 0 | chunk 1 << 16 (at most 1024 each)
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < F4; ++j) {
     if (in[j]) {
       f4v q;
       q.x = a[j].x + gg[j].x;
       q.y = a[j].y + gg[j].y;
       q.z = a[j].z + gg[j].z;
       q.w = a[j].w + gg[j].w;
-      store_quad<RAG>(A + x0 + 1024u * j, q, in[j]);
+      store_quad<RAG>(A + x0 + (uint32_t)(CH * j), q, in[j]);
       r[4 * j + 0] = q.x;
       r[4 * j + 1] = q.y;
       r[4 * j + 2] = q.z;
@@ -417,14 +433,14 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   __syncthreads();   // also ends the histogram's updates
   uint32_t base = 0, tot = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < NW; ++k) {
     const uint32_t x = wtot[k];
     base += k < wv ? x : 0u;
     tot += x;
   }
   {
     uint32_t* __restrict__ H = sp.hist1 + ((int64_t)wb * sp.hcopies + (g & (sp.hcopies - 1u))) * NB1;   // a power of 2
-    flush_hist<256>(h, H);
+    flush_hist<NT>(h, H);
   }
   const uint32_t tot0 = tot & 0xFFFFu, all = tot0 + (tot >> 16);
   const uint32_t ex = base + incl - packed;
@@ -436,12 +452,12 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
   float* __restrict__ oV = staged ? s_val : CV;
   if (packed != 0u) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < F4; ++j) {
       uint32_t pos = j == 0 ? (ex & 0xFFFFu) : tot0 + (ex >> 16);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         if ((RAG ? ((in[j] >> c) & 1u) != 0u : in[j] != 0u) && mag_key(r[4 * j + c]) >= F) {
-          oI[pos] = (int32_t)(x0 + 1024u * j + (uint32_t)c);
+          oI[pos] = (int32_t)(x0 + (uint32_t)(CH * j + c));
           oV[pos] = r[4 * j + c];
           ++pos;
         }
@@ -454,7 +470,7 @@ __global__ __launch_bounds__(256) void k_residual_add4(float* __restrict__ acc, 
     // whole lines: pad the run to a multiple of 32 entries, inside the tile's span
     const uint32_t span = min(e, ta + (uint32_t)ADD_TILE) - t0;
     const uint32_t padded = min((all + 31u) & ~31u, span);
-    for (uint32_t k = threadIdx.x; k < padded; k += 256) {
+    for (uint32_t k = threadIdx.x; k < padded; k += NT) {
       __builtin_nontemporal_store(s_idx[k], CI + k);
       __builtin_nontemporal_store(s_val[k], CV + k);
     }
@@ -476,7 +492,7 @@ __global__ __launch_bounds__(256) void k_hist1(const float* __restrict__ acc, in
   __syncthreads();
   const float* __restrict__ A = acc + (int64_t)w * ld_acc;
 #pragma unroll
-  for (int j = 0; j < ADD_F4; ++j) {
+  for (int j = 0; j < ADD_TILE / 1024; ++j) {
     const uint32_t off = t0 + (j * 256u + threadIdx.x) * 4u;
     if (off < e && e - off >= 4u) {
       const f4v a = *reinterpret_cast<const f4u*>(A + off);
@@ -518,7 +534,8 @@ hipError_t launch_residual_add(float* acc, int64_t ld_acc, const float* grad, in
     // at most 65535 rows per launch (with HIST there are at most P rows, and a workspace holds far fewer)
     constexpr int32_t ROWS = 65535;
     for (int32_t w = 0; w < nworkers; w += ROWS)
-      hipLaunchKernelGGL(kernel, dim3(G, (unsigned)PP, (unsigned)std::min(nworkers - w, ROWS)), dim3(256), 0, s,
+      hipLaunchKernelGGL(kernel, dim3(G, (unsigned)PP, (unsigned)std::min(nworkers - w, ROWS)),
+                         dim3((unsigned)add_threads(C.member != nullptr)), 0, s,
                          acc + w * ld_acc, ld_acc, grad + w * ld_grad, ld_grad, B, G, spc, C);
   };
   auto pick = [&](auto even, auto ragged, auto brief) { vec4 ? go(even) : n >= 4 ? go(ragged) : go(brief); };
