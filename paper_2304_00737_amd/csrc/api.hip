@@ -172,6 +172,22 @@ Ws carve(void* ws, size_t ws_bytes, const Layout& L) {
   return w;
 }
 
+// Whether the add that follows a step applies that step's residual collection
+// to its tiles (k_residual_add4 with COLL); otherwise the collection's own
+// kernels run before the plain add, with the same results.  In the tiles it
+// costs time per element streamed, on its own time per entry selected or
+// dropped, scattered, and a launch per SRS step, so it goes into the add for
+// small steps and dense ones.  Whole steps, in the add and apart: P = 8, n =
+// 25.6M at 1 % 619 and 617 us; n = 138M at 0.5 % 2822 and 2672; P = 16, n =
+// 110M at 1 % 4489 and 4394; P = 14, n = 20,033,001 at 1 % 856 and 822; P =
+// 4, n = 50M at 0.1 % 584 and 566, at 1.5 % 677 and 677; but P = 8, n = 8.4M
+// at 1 % 282 and 288, at 0.3 % 243 and 251; P = 6, n = 15M at 10 % 571 and
+// 603.
+bool collect_in_add(int32_t P, int64_t n, int32_t kb, int32_t l) {
+  if (l > COLLECT_MAX_STEPS) return false;   // more SRS steps than the add takes
+  return (int64_t)P * n < (1ll << 27) || 64ll * kb * P > n;
+}
+
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 inline bool ws_misaligned(const void* ws) { return ((uintptr_t)ws & 255u) != 0; }
 
@@ -502,8 +518,7 @@ int spardl_residual_add_collect(float* acc, int64_t ld_acc, const float* grad, i
   sp.spec_cnt = w.spec_cnt;
   sp.cand_idx = w.cand_idx;
   sp.cand_val = w.cand_val;
-  if (l > COLLECT_MAX_STEPS) {
-    // more SRS steps than the add's collection takes: the separate collection of these rows, then the add
+  if (!collect_in_add(P, n, k_blk, l)) {
     SPARDL_TRY(launch_grc_zero(acc, ld_acc, nworkers, P, n, k_blk, local_idx, member, stream));
     for (int32_t i = 1; i <= l; ++i) {
       const int32_t m = bag_of(P, l, i);
@@ -533,7 +548,7 @@ int spardl_residual_collect_index(int32_t w0, int32_t nworkers, int64_t n, int32
   const size_t need = spardl_workspace_bytes(1, P, n, k_blk);
   if (need == 0) return SPARDL_EINVAL;
   if (ws_bytes < need) return SPARDL_ECAPACITY;
-  if (l == 0 || l > COLLECT_MAX_STEPS) return SPARDL_OK;   // the add collects without an index
+  if (l == 0 || !collect_in_add(P, n, k_blk, l)) return SPARDL_OK;   // the add collects without an index
   const Layout L = make_layout(P, n, k_blk);
   Ws w = carve(ws, ws_bytes, L);
   std::vector<const float*> no_val(l, nullptr);
