@@ -29,19 +29,22 @@ namespace spardl {
 // block's full histogram of the top 12 key bits from acc.  A full histogram
 // must hold exactly the block's entries.  The threshold bin goes to the state
 // as a key prefix and its shift (ST_T1, ST_SHIFT).
-__global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, uint32_t* __restrict__ state,
-                                                  Blocks B, Units U, uint32_t need, uint32_t* __restrict__ spec_t1,
-                                                  const uint32_t* __restrict__ spec_used, int spec,
-                                                  const float* __restrict__ acc, int64_t ld_acc,
-                                                  uint32_t hc, uint32_t* __restrict__ err) {
-  constexpr int NT = 1024, PER = NB1 / NT;
+struct Level1 {
+  uint32_t pfx, S;      // the threshold bin: the keys k with k >> S == pfx
+  uint32_t above, cnt;  // entries above the bin, and in it
+  uint32_t ok;          // 0: no threshold found
+};
+
+// By a workgroup of NT threads (every thread gets the answer); h: NB1 words of
+// LDS, scratch: NT / WAVE + 4.  H: the block's hc copies, cleared if CLEAR.
+// may_recount: if false, ok = 0 where the block has to be counted from acc.
+// report: whether a histogram that cannot be the block's sets the error word.
+template <int NT, bool CLEAR>
+__device__ __forceinline__ Level1 block_level1(uint32_t* __restrict__ H, uint32_t hc, uint32_t used, uint32_t need,
+                                               const float* __restrict__ A, uint32_t s, uint32_t e, bool may_recount,
+                                               bool report, uint32_t* h, uint32_t* scratch, uint32_t* __restrict__ err) {
+  constexpr int PER = NB1 / NT;
   static_assert(HCOPIES_MIN == 4, "copies are summed four at a time");
-  __shared__ uint32_t h[NB1];
-  __shared__ uint32_t scratch[24];
-  uint32_t w, b;
-  U.decode(blockIdx.x, B.P, &w, &b);
-  const int64_t u = (int64_t)w * B.P + b;   // the block's arrays
-  uint32_t* __restrict__ H = hist1 + u * hc * NB1;
   uint32_t c[PER];
 #pragma unroll
   for (int q = 0; q < PER; ++q) c[q] = 0u;
@@ -56,25 +59,28 @@ __global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, 
 #pragma unroll
       for (uint32_t k = 0; k < HCOPIES_MIN; ++k) {
         c[q] += r[q][k];
-        H[(k0 + k) * NB1 + q * NT + threadIdx.x] = 0u;
+        if (CLEAR) H[(k0 + k) * NB1 + q * NT + threadIdx.x] = 0u;
       }
   }
 #pragma unroll
   for (int q = 0; q < PER; ++q) h[q * NT + threadIdx.x] = c[q];
-  const uint32_t used = spec ? spec_used[u] : SPEC_NONE;
   const L1Map M = l1_map(used);
   __syncthreads();
-  uint32_t T, above, cnt, ok, total;
-  block_select_desc(h, NB1, need, scratch, &T, &above, &cnt, &ok, &total);
-  const uint32_t s = B.start(b), e = B.start(b + 1u);
+  Level1 R;
+  uint32_t T, total;
+  block_select_desc(h, NB1, need, scratch, &T, &R.above, &R.cnt, &R.ok, &total);
   bool full = !M.fine;   // the top-12-bit histogram of every key
-  uint32_t pfx = T, S = D1_SHIFT;   // the threshold bin: the keys k with k >> S == pfx
+  R.pfx = T;
+  R.S = D1_SHIFT;
   // the threshold fell below the histogram's floor, or above its fine window:
   // count the whole block by its top 12 key bits
-  if (!full && (!ok || !M.bin_keys(T, &pfx, &S))) {
+  if (!full && (!R.ok || !M.bin_keys(T, &R.pfx, &R.S))) {
+    if (!may_recount) {
+      R.ok = 0u;
+      return R;
+    }
     for (int i = threadIdx.x; i < NB1; i += NT) h[i] = 0u;
     __syncthreads();
-    const float* __restrict__ A = acc + (int64_t)w * ld_acc;
     for (uint32_t x0 = s + threadIdx.x * 4u; x0 < e; x0 += NT * 4u * 4u) {
       f4v v[4];
 #pragma unroll
@@ -96,24 +102,40 @@ __global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, 
       }
     }
     __syncthreads();
-    block_select_desc(h, NB1, need, scratch, &T, &above, &cnt, &ok, &total);
+    block_select_desc(h, NB1, need, scratch, &T, &R.above, &R.cnt, &R.ok, &total);
     full = true;
-    pfx = T;
-    S = D1_SHIFT;
+    R.pfx = T;
+    R.S = D1_SHIFT;
   }
+  const uint32_t len = e - s;
+  if (threadIdx.x == 0 && report && (!R.ok || (full ? total != len : total > len))) atomicOr(err, ERR_COUNT);
+  return R;
+}
+
+__global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, uint32_t* __restrict__ state,
+                                                  Blocks B, Units U, uint32_t need, uint32_t* __restrict__ spec_t1,
+                                                  const uint32_t* __restrict__ spec_used, int spec,
+                                                  const float* __restrict__ acc, int64_t ld_acc,
+                                                  uint32_t hc, uint32_t* __restrict__ err) {
+  __shared__ uint32_t h[NB1];
+  __shared__ uint32_t scratch[24];
+  uint32_t w, b;
+  U.decode(blockIdx.x, B.P, &w, &b);
+  const int64_t u = (int64_t)w * B.P + b;   // the block's arrays
+  const uint32_t used = spec ? spec_used[u] : SPEC_NONE;
+  const Level1 R = block_level1<1024, true>(hist1 + u * hc * NB1, hc, used, need, acc + (int64_t)w * ld_acc, B.start(b),
+                                            B.start(b + 1u), true, true, h, scratch, err);
   if (threadIdx.x == 0) {
     uint32_t* st = state + u * ST_WORDS;
-    const uint32_t len = e - s;
-    if (!ok || (full ? total != len : total > len)) atomicOr(err, ERR_COUNT);
     // the fused add's speculative candidates hold every key >= its floor, so
     // they are usable when the floor is at or below the threshold bin
-    st[ST_SPECOK] = (spec && ok && used <= (pfx << S)) ? 1u : 0u;
-    if (spec_t1) spec_t1[u] = ok ? ((pfx << S) >> D1_SHIFT) + 1u : 0u;   // the next add's floor: 12-bit bins
-    st[ST_T1] = pfx;
-    st[ST_SHIFT] = S;
-    st[ST_ABOVE1] = above;
-    st[ST_NEED1] = ok ? need - above : 0u;
-    st[ST_CNT1] = cnt;
+    st[ST_SPECOK] = (spec && R.ok && used <= (R.pfx << R.S)) ? 1u : 0u;
+    if (spec_t1) spec_t1[u] = R.ok ? ((R.pfx << R.S) >> D1_SHIFT) + 1u : 0u;   // the next add's floor: 12-bit bins
+    st[ST_T1] = R.pfx;
+    st[ST_SHIFT] = R.S;
+    st[ST_ABOVE1] = R.above;
+    st[ST_NEED1] = R.ok ? need - R.above : 0u;
+    st[ST_CNT1] = R.cnt;
   }
 }
 
@@ -184,9 +206,10 @@ struct CollectSmem {
   uint32_t cb[SLOT / 256 * 4 + 1];   // ... and threshold-bin entries
 };
 
-template <bool FULL>
+// bin(&tlo, &S): the threshold bin's first key and its shift.
+template <bool FULL, typename Bin>
 __device__ __forceinline__ void collect_slot(const float* __restrict__ A, uint32_t nvalid, int32_t pos0,
-                                             const uint32_t* __restrict__ st, CollectSmem& L,
+                                             Bin bin, CollectSmem& L,
                                              uint32_t* cnt_out, uint32_t* nbin_out, int32_t* __restrict__ CI,
                                              float* __restrict__ CV, uint32_t* __restrict__ BK) {
   constexpr int PT = SLOT / 256;
@@ -211,8 +234,8 @@ __device__ __forceinline__ void collect_slot(const float* __restrict__ A, uint32
   }
   // the threshold bin is read only now, so its latency overlaps the data loads
   __builtin_amdgcn_sched_barrier(0);
-  const uint32_t S = st[ST_SHIFT];
-  const uint32_t tlo = st[ST_T1] << S;
+  uint32_t S, tlo;
+  bin(&tlo, &S);
   const uint32_t thi = tlo + (1u << S);   // the bin's keys are below 2^31, so this fits in 32 bits
   uint32_t tc = 0, tb = 0;
 #pragma unroll
@@ -266,6 +289,34 @@ __device__ __forceinline__ void collect_slot(const float* __restrict__ A, uint32
       CV[j] = L.sv[j];
     }
     for (uint32_t j = threadIdx.x; j < nbin; j += 256) BK[j] = L.sk[j];
+  }
+}
+
+// Slots slot0 .. slot0 + count - 1 of block [s, e) of row A (row w of n, the
+// block's arrays at `unit`), one after another, by a workgroup of 256 threads.
+template <typename Bin>
+__device__ __forceinline__ void collect_slots(const float* __restrict__ A, uint32_t n, uint32_t w, uint32_t unit,
+                                              uint32_t s, uint32_t e, uint32_t slot0, uint32_t count, uint32_t smax,
+                                              Bin bin, CollectSmem& L, uint32_t* __restrict__ slot_cnt,
+                                              uint32_t* __restrict__ slot_nbin, int32_t* __restrict__ cand_idx,
+                                              float* __restrict__ cand_val, uint32_t* __restrict__ bin_key) {
+  const uint32_t o = block_origin(s);
+  for (uint32_t k = 0; k < count; ++k) {
+    const uint32_t slot = slot0 + k;
+    if (slot >= smax || o + slot * (uint32_t)SLOT >= e) break;   // uniform
+    if (k > 0u) __syncthreads();          // LDS reuse
+    const uint32_t sa = o + slot * (uint32_t)SLOT;
+    const uint32_t t0 = sa > s ? sa : s;
+    const uint32_t hi = sa + (uint32_t)SLOT;
+    const uint32_t nvalid = (hi < e ? hi : e) - t0;   // entries of this slot inside the block
+    const int64_t cbase = (int64_t)w * n + t0;
+    const int64_t si = (int64_t)unit * smax + slot;
+    if (nvalid == (uint32_t)SLOT)
+      collect_slot<true>(A + t0, nvalid, (int32_t)t0, bin, L, slot_cnt + si, slot_nbin + si, cand_idx + cbase,
+                         cand_val + cbase, bin_key + cbase);
+    else
+      collect_slot<false>(A + t0, nvalid, (int32_t)t0, bin, L, slot_cnt + si, slot_nbin + si, cand_idx + cbase,
+                          cand_val + cbase, bin_key + cbase);
   }
 }
 
@@ -496,24 +547,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPW >= 8 ? 
       return;
     }
   }
-  for (int k = 0; k < COLLECT_GROUP; ++k) {
-    const uint32_t slot = slot0 + (uint32_t)k;
-    if (slot >= smax || o + slot * (uint32_t)SLOT >= e) break;   // uniform
-    if (k > 0) __syncthreads();           // LDS reuse
-    const uint32_t sa = o + slot * (uint32_t)SLOT;
-    const uint32_t t0 = sa > s ? sa : s;
-    const uint32_t hi = sa + (uint32_t)SLOT;
-    const uint32_t nvalid = (hi < e ? hi : e) - t0;   // entries of this slot inside the block
-    const float* __restrict__ A = acc + (int64_t)w * ld_acc + t0;
-    const int64_t cbase = (int64_t)w * B.n + t0;
-    const int64_t si = (int64_t)unit * smax + slot;
-    if (nvalid == (uint32_t)SLOT)
-      collect_slot<true>(A, nvalid, (int32_t)t0, st, L, slot_cnt + si, slot_nbin + si,
-                              cand_idx + cbase, cand_val + cbase, bin_key + cbase);
-    else
-      collect_slot<false>(A, nvalid, (int32_t)t0, st, L, slot_cnt + si, slot_nbin + si,
-                               cand_idx + cbase, cand_val + cbase, bin_key + cbase);
-  }
+  collect_slots(acc + (int64_t)w * ld_acc, B.n, w, unit, s, e, slot0, (uint32_t)COLLECT_GROUP, smax,
+                [&](uint32_t* tlo, uint32_t* S) {
+                  *S = st[ST_SHIFT];
+                  *tlo = st[ST_T1] << *S;
+                },
+                L, slot_cnt, slot_nbin, cand_idx, cand_val, bin_key);
 }
 
 // ============================================================================ exact threshold
@@ -1755,7 +1794,368 @@ __global__ __launch_bounds__(256) void k_emit(
   }
 }
 
+// ============================================================================ a3 in one workgroup per block
+// A block that selects few entries (topk_one below) has its candidates in one
+// workgroup's registers: the fused add's, when they hold the whole selection
+// (at least `need` keys at or above the floor), else those the block's own
+// level-1 threshold leaves.  One launch then finds the exact threshold and
+// writes the selection, where the general path takes four dependent ones, each
+// mostly waiting; what it writes is the same.  A block the candidates do not
+// decide (its first step, a fallen threshold, entries changed since the add) is
+// first reduced to them: by k_one_prep, with workgroups enough to stream it,
+// or, up to ONE_SELF elements, by the same workgroup.  It is bound by the
+// chain of barriers and by one CU's instruction issue (a tile list's search, 7
+// to 10 LDS reads, is most of it), which is why it ends at ONE_KB entries.  The
+// four launches and this: 26 and 9 us for 16 blocks of 16384 at 1 %, 28 and
+// 22 us for 16 of 2^18 at 1 %, 33 and 20 us for 32 of 1.25M at 0.1 %, 42 and
+// 17 us for 256 of 100,000 at 1 %.
+constexpr int ONE_THREADS = 1024;
+constexpr int ONE_R = 16;                            // candidates per thread in registers
+constexpr int ONE_CAP = ONE_THREADS * ONE_R;         // a chunk; further chunks are loaded again per pass
+constexpr int ONE_LISTS = ONE_THREADS;               // most add tiles per block: a list per thread
+constexpr int ONE_KB = 4096;                         // most entries selected (staged in LDS)
+constexpr int64_t ONE_SELF = 1 << 16;
+constexpr uint32_t PREP_SLOTS = 8;                   // slots per workgroup of k_one_prep
+
+struct TopkOne {
+  const float* acc;
+  int64_t ld_acc;
+  Blocks B;
+  Units U;
+  uint32_t kb, smax, add_tiles, hc;
+  int spec, self;
+  uint32_t *hist1, *state, *slot_cnt, *slot_nbin, *spec_t1, *keep, *err;
+  const uint32_t *spec_used, *spec_cnt;
+  int32_t* cand_idx;
+  float* cand_val;
+  uint32_t* bin_key;
+  int32_t *out_idx, *local_idx;
+  float* out_val;
+};
+
+// The candidates the fused add left in tile g of block [s, e) (array index u):
+// at most the tile's elements.
+__device__ __forceinline__ uint32_t tile_candidates(const TopkOne& a, int64_t u, uint32_t s, uint32_t e, uint32_t g) {
+  const uint32_t t0 = block_origin(s) + g * (uint32_t)ADD_TILE, t1 = t0 + (uint32_t)ADD_TILE;
+  return min(a.spec_cnt[u * a.add_tiles + g], min(t1, e) - max(t0, s));
+}
+__device__ __forceinline__ uint32_t tiles_of(uint32_t s, uint32_t e) {
+  return (e - block_origin(s) + (uint32_t)ADD_TILE - 1u) / (uint32_t)ADD_TILE;
+}
+// Whether a block with this word of the add has candidates at all.
+__device__ __forceinline__ bool spec_valid(uint32_t used) { return used != SPEC_NONE && !(used & SPEC_DIRTY); }
+
+// The blocks their candidates do not decide: level-1 threshold, then the
+// block's entries at or above its bin into its slots, PREP_SLOTS per
+// workgroup.  Every workgroup of a block finds the threshold itself; a block
+// that has to be counted again is left to its first one.
+__global__ __launch_bounds__(256) void k_one_prep(TopkOne a, uint32_t gq) {
+  __shared__ uint32_t h[NB1];
+  __shared__ CollectSmem L;
+  __shared__ uint32_t scratch[16];
+  uint32_t w, b;
+  a.U.decode(blockIdx.x / gq, a.B.P, &w, &b);
+  const int64_t u = (int64_t)w * a.B.P + b;
+  const uint32_t s = a.B.start(b), e = a.B.start(b + 1u);
+  const uint32_t used = a.spec ? a.spec_used[u] : SPEC_NONE;
+  if (spec_valid(used)) {
+    uint32_t c = 0u, total;
+    const uint32_t nt = tiles_of(s, e);
+    for (uint32_t g = threadIdx.x; g < nt; g += 256u) c += tile_candidates(a, u, s, e, g);
+    block_excl_scan(c, scratch, &total);
+    if (total >= a.kb) return;   // uniform
+  }
+  const uint32_t slot0 = (blockIdx.x % gq) * PREP_SLOTS;
+  if (block_origin(s) + slot0 * (uint32_t)SLOT >= e) return;
+  const float* __restrict__ A = a.acc + (int64_t)w * a.ld_acc;
+  // counted again only by the first workgroup, which then takes the whole block
+  Level1 R = block_level1<256, false>(a.hist1 + u * a.hc * NB1, a.hc, used, a.kb, A, s, e, false, slot0 == 0u, h, scratch,
+                                     a.err);
+  uint32_t count = PREP_SLOTS;
+  if (!R.ok) {   // uniform
+    if (slot0 != 0u) return;
+    __syncthreads();
+    R = block_level1<256, false>(a.hist1 + u * a.hc * NB1, a.hc, used, a.kb, A, s, e, true, true, h, scratch, a.err);
+    count = a.smax;
+  }
+  if (slot0 == 0u && threadIdx.x == 0) {
+    uint32_t* st = a.state + u * ST_WORDS;
+    st[ST_T1] = R.pfx;
+    st[ST_SHIFT] = R.S;
+  }
+  collect_slots(A, a.B.n, w, (uint32_t)u, s, e, slot0, count, a.smax,
+                [&](uint32_t* tlo, uint32_t* S) {
+                  *S = R.S;
+                  *tlo = R.pfx << R.S;
+                },
+                L, a.slot_cnt, a.slot_nbin, a.cand_idx, a.cand_val, a.bin_key);
+}
+
+__global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
+  __shared__ uint32_t h[NB1];
+  __shared__ float ov[ONE_KB];
+  __shared__ uint32_t pref[ONE_LISTS + 1];
+  __shared__ uint32_t cw[ONE_R * ONE_THREADS / WAVE];   // emit: per (register, wave) the counts, then those before it
+  __shared__ uint32_t scratch[24];
+  static_assert(ONE_KB <= NB1, "the selected indices are staged in the histogram's space");
+  const uint32_t t = threadIdx.x;
+  uint32_t w, b;
+  a.U.decode(blockIdx.x, a.B.P, &w, &b);
+  const int64_t u = (int64_t)w * a.B.P + b;
+  const uint32_t s = a.B.start(b), e = a.B.start(b + 1u), o = block_origin(s);
+  uint32_t* st = a.state + u * ST_WORDS;
+  uint32_t* __restrict__ H = a.hist1 + u * a.hc * NB1;
+  int32_t* __restrict__ CI = a.cand_idx + (int64_t)w * a.B.n;
+  float* __restrict__ CV = a.cand_val + (int64_t)w * a.B.n;
+
+  // ---- the candidates: nl lists, list i from max(o + i lw, s) on, of pref[i + 1] - pref[i] entries; the
+  // smallest key they may hold
+  const uint32_t used = a.spec ? a.spec_used[u] : SPEC_NONE;
+  uint32_t nl = tiles_of(s, e), lw = (uint32_t)ADD_TILE, key0 = used, N;
+  uint32_t c0 = t < nl ? tile_candidates(a, u, s, e, t) : 0u;   // (loaded with the word before)
+  const bool valid = spec_valid(used);   // uniform
+  if (!valid) c0 = 0u;
+  uint32_t ex = block_excl_scan(c0, scratch, &N);
+  const bool specok = valid && N >= a.kb;   // uniform
+  if (!specok && a.self) {
+    const float* __restrict__ A = a.acc + (int64_t)w * a.ld_acc;
+    const Level1 R = block_level1<ONE_THREADS, false>(H, a.hc, used, a.kb, A, s, e, true, true, h, scratch, a.err);
+    key0 = R.pfx << R.S;
+    nl = 1u;
+    N = 0u;
+    for (uint32_t x0 = s; x0 < e; x0 += (uint32_t)ONE_CAP) {   // uniform
+      const uint32_t x = x0 + t * (uint32_t)ONE_R;
+      f4v v[ONE_R / 4];
+#pragma unroll
+      for (int q = 0; q < ONE_R / 4; ++q) {
+        const uint32_t y = x + (uint32_t)(4 * q);
+        v[q] = f4v{0.f, 0.f, 0.f, 0.f};
+        if (y < e && e - y >= 4u) {
+          v[q] = *reinterpret_cast<const f4u*>(A + y);
+        } else if (y < e) {   // the block's last elements
+          v[q].x = A[y];
+          if (y + 1u < e) v[q].y = A[y + 1u];
+          if (y + 2u < e) v[q].z = A[y + 2u];
+        }
+      }
+      uint32_t c = 0u, tot;
+#pragma unroll
+      for (int r = 0; r < ONE_R; ++r) c += x + (uint32_t)r < e && mag_key(v[r / 4][r % 4]) >= key0 ? 1u : 0u;
+      uint32_t pos = N + block_excl_scan(c, scratch, &tot);
+#pragma unroll
+      for (int r = 0; r < ONE_R; ++r) {
+        if (x + (uint32_t)r < e && mag_key(v[r / 4][r % 4]) >= key0) {
+          CI[s + pos] = (int32_t)(x + (uint32_t)r);
+          CV[s + pos] = v[r / 4][r % 4];
+          ++pos;
+        }
+      }
+      N += tot;
+    }
+    ex = 0u;
+  } else if (!specok) {
+    key0 = st[ST_T1] << st[ST_SHIFT];
+    lw = (uint32_t)SLOT;
+    nl = (e - o + lw - 1u) / lw;
+    uint32_t c = 0u;
+    if (t < nl) {
+      const uint32_t x0 = o + t * lw;
+      c = min(a.slot_cnt[u * a.smax + t], min(x0 + lw, e) - max(x0, s));
+    }
+    ex = block_excl_scan(c, scratch, &N);
+  }
+  if (t < nl) pref[t] = ex;
+  if (t == 0) pref[nl] = N;
+  __syncthreads();   // also: the candidates this workgroup wrote
+  // ---- chunk c of the candidates in registers: entry e0 + r ONE_THREADS in register r (whole lines per
+  // wave).  One CU runs all of this, so instructions count: registers past the chunk's entries are
+  // skipped by uniform branches.
+  N = (uint32_t)__builtin_amdgcn_readfirstlane((int)N);
+  const uint32_t nch = (N + (uint32_t)ONE_CAP - 1u) / (uint32_t)ONE_CAP;
+  int32_t ix[ONE_R];
+  float vx[ONE_R];
+  uint32_t e0 = 0u, per = 0u;   // per: registers in use (uniform)
+  auto load = [&](uint32_t c) {
+    e0 = c * (uint32_t)ONE_CAP + t;
+    per = (min(N - c * (uint32_t)ONE_CAP, (uint32_t)ONE_CAP) + ONE_THREADS - 1u) / ONE_THREADS;
+#pragma unroll
+    for (int r = 0; r < ONE_R; ++r) {
+      if ((uint32_t)r < per) {   // uniform
+        const uint32_t f = min(e0 + (uint32_t)(r * ONE_THREADS), N - 1u);
+        uint32_t lo = 0u, hi = nl;   // the last list that starts at or before f
+        while (hi - lo > 1u) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (pref[mid] <= f) lo = mid;
+          else hi = mid;
+        }
+        const uint32_t at = max(o + lo * lw, s) + (f - pref[lo]);
+        ix[r] = CI[at];
+        vx[r] = CV[at];
+      }
+    }
+  };
+  auto each = [&](auto f) {   // f(key) for every candidate
+    for (uint32_t c = 0; c < nch; ++c) {
+      if (nch > 1u) load(c);   // uniform
+#pragma unroll
+      for (int r = 0; r < ONE_R; ++r) {
+        if ((uint32_t)r < per) {   // uniform
+          if (e0 + (uint32_t)(r * ONE_THREADS) < N) f(mag_key(vx[r]));
+        }
+      }
+    }
+  };
+  if (nch > 0u) load(0u);
+
+  // ---- level 1: bins of 2^FINE_SHIFT keys from the smallest candidate key on, the last also holding every
+  // larger key; if the threshold falls there, bins of the top 12 key bits
+#pragma unroll
+  for (int q = 0; q < NB1 / ONE_THREADS; ++q) h[q * ONE_THREADS + (int)t] = 0u;
+  __syncthreads();
+  const uint32_t f0 = key0 >> FINE_SHIFT;
+  each([&](uint32_t key) { atomicAdd(&h[min((key >> FINE_SHIFT) - f0, (uint32_t)NB1 - 1u)], 1u); });
+  __syncthreads();
+  // the histogram copies rest at zero between steps (cleared here, behind the
+  // loads: a load issued after stores is waited for with them)
+  for (uint32_t i = t; i < a.hc * (uint32_t)(NB1 / 4); i += ONE_THREADS) reinterpret_cast<uint4*>(H)[i] = make_uint4(0u, 0u, 0u, 0u);
+  uint32_t T, above, cnt, ok;
+  block_select_desc(h, NB1, a.kb, scratch, &T, &above, &cnt, &ok);
+  int S = FINE_SHIFT;
+  uint32_t pfx = f0 + T;
+  if (T == (uint32_t)NB1 - 1u) {   // uniform
+#pragma unroll
+    for (int q = 0; q < NB1 / ONE_THREADS; ++q) h[q * ONE_THREADS + (int)t] = 0u;
+    __syncthreads();
+    each([&](uint32_t key) { atomicAdd(&h[key >> D1_SHIFT], 1u); });
+    __syncthreads();
+    block_select_desc(h, NB1, a.kb, scratch, &T, &above, &cnt, &ok);
+    S = D1_SHIFT;
+    pfx = T;
+  }
+  if (!ok && t == 0) atomicOr(a.err, ERR_COUNT);
+  uint32_t tge, teq, need_eq;
+  resolve_bin(pfx, S, ok ? a.kb - above : 0u, ok ? cnt : 0u, h, scratch, a.err,
+              [&](auto f) {
+                each([&](uint32_t key) {
+                  if ((key >> S) == pfx) f(key);
+                });
+              },
+              tge, teq, need_eq);
+
+  // ---- emit in index order: an entry's place is the entries >= TGE before it plus the ties taken before
+  // it; staged in LDS, then written as whole lines
+  const int lane = lane_id(), wv = wave_id();
+  const uint64_t lt = __lanemask_lt();
+  constexpr uint32_t NWV = ONE_THREADS / WAVE;
+  int32_t* oi = reinterpret_cast<int32_t*>(h);
+  uint32_t run_g = 0u, run_e = 0u;
+  __syncthreads();   // the histogram's space is read no more
+  for (uint32_t c = 0; c < nch; ++c) {
+    if (nch > 1u) load(c);   // uniform
+#pragma unroll
+    for (int r = 0; r < ONE_R; ++r) {
+      if ((uint32_t)r < per) {   // uniform
+        const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
+        const uint32_t key = mag_key(vx[r]);
+        const uint32_t g = popc64(__ballot(live && key >= tge));
+        const uint32_t q = popc64(__ballot(live && need_eq != 0u && key == teq));
+        if (lane == 0) cw[(uint32_t)r * NWV + (uint32_t)wv] = g | (q << 16);
+      }
+    }
+    __syncthreads();
+    static_assert(ONE_CAP < (1 << 16), "packed counts of a chunk");
+    uint32_t tot;
+    const uint32_t mine = t < per * NWV ? cw[t] : 0u;
+    const uint32_t before = block_excl_scan(mine, scratch, &tot);
+    if (t < per * NWV) cw[t] = before;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ONE_R; ++r) {
+      if ((uint32_t)r < per) {   // uniform
+        const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
+        const uint32_t key = mag_key(vx[r]);
+        const bool is_ge = live && key >= tge, is_eq = live && need_eq != 0u && key == teq;
+        const uint64_t mg = __ballot(is_ge), me = __ballot(is_eq);
+        const uint32_t x = cw[(uint32_t)r * NWV + (uint32_t)wv];
+        const uint32_t gp = run_g + (x & 0xFFFFu) + popc64(mg & lt), ep = run_e + (x >> 16) + popc64(me & lt);
+        if (a.keep && is_eq && ep + 1u == need_eq) a.keep[u * KEEP_WORDS + KEEP_CUT] = (uint32_t)ix[r];   // the last tie taken
+        if (is_ge || (is_eq && ep < need_eq)) {
+          const uint32_t pos = gp + min(ep, need_eq);
+          if (pos < a.kb) {
+            oi[pos] = ix[r];
+            ov[pos] = vx[r];
+          } else {
+            atomicOr(a.err, ERR_COUNT_POS);
+          }
+        }
+      }
+    }
+    run_g += tot & 0xFFFFu;
+    run_e += tot >> 16;
+    __syncthreads();   // cw is written again
+  }
+  const uint32_t taken = run_g + min(run_e, need_eq);
+  const int64_t out = u * a.kb;
+  for (uint32_t i = t; i < min(a.kb, taken); i += ONE_THREADS) {
+    a.out_idx[out + i] = oi[i];
+    a.out_val[out + i] = ov[i];
+    if (a.local_idx) a.local_idx[out + i] = oi[i];
+  }
+  if (t == 0) {
+    if (taken != a.kb) atomicOr(a.err, ERR_COUNT_SUM);
+    st[ST_SPECOK] = specok ? 1u : 0u;
+    if (a.spec_t1) a.spec_t1[u] = ok ? ((pfx << S) >> D1_SHIFT) + 1u : 0u;   // the next add's floor: 12-bit bins
+    if (a.keep) {
+      uint32_t* kp = a.keep + u * KEEP_WORDS;
+      kp[KEEP_TGE] = tge;
+      kp[KEEP_TEQ] = teq;
+      kp[KEEP_NEEDEQ] = need_eq;
+    }
+  }
+}
+
 // ============================================================================ launchers
+hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
+                           int32_t kb, int32_t smax, int32_t add_tiles, bool spec, uint32_t* hist1, uint32_t* state,
+                           uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt, uint32_t* slot_cnt,
+                           uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val, uint32_t* bin_key, int32_t* out_idx,
+                           float* out_val, int32_t* local_idx, uint32_t* keep, uint32_t* err, hipStream_t s) {
+  TopkOne a;
+  a.acc = acc;
+  a.ld_acc = ld_acc;
+  a.B = make_blocks(n, P);
+  a.U = U;
+  a.kb = (uint32_t)kb;
+  a.smax = (uint32_t)smax;
+  a.add_tiles = (uint32_t)add_tiles;
+  a.hc = hist_copies_for(n, P);
+  a.spec = spec ? 1 : 0;
+  a.self = (n + P - 1) / P <= ONE_SELF ? 1 : 0;
+  a.hist1 = hist1;
+  a.state = state;
+  a.slot_cnt = slot_cnt;
+  a.slot_nbin = slot_nbin;
+  a.spec_t1 = spec_t1;
+  a.keep = keep;
+  a.err = err;
+  a.spec_used = spec_used;
+  a.spec_cnt = spec_cnt;
+  a.cand_idx = cand_idx;
+  a.cand_val = cand_val;
+  a.bin_key = bin_key;
+  a.out_idx = out_idx;
+  a.local_idx = local_idx;
+  a.out_val = out_val;
+  if (!a.self) {
+    const uint32_t gq = ((uint32_t)smax + PREP_SLOTS - 1u) / PREP_SLOTS;
+    hipLaunchKernelGGL(k_one_prep, dim3((unsigned)(nunits * gq)), dim3(256), 0, s, a, gq);
+  }
+  hipLaunchKernelGGL(k_topk_one, dim3((unsigned)nunits), dim3(ONE_THREADS), 0, s, a);
+  return hipGetLastError();
+}
+
+bool topk_one(int32_t kb, int64_t add_tiles) { return kb <= ONE_KB && add_tiles <= ONE_LISTS; }
+
 hipError_t launch_select1(uint32_t* hist1, uint32_t* state, int64_t nunits, const Units& U, int64_t n, int32_t P,
                           uint32_t need, uint32_t* spec_t1, const uint32_t* spec_used, bool spec, const float* acc,
                           int64_t ld_acc, uint32_t* err, hipStream_t s) {
