@@ -98,8 +98,8 @@ __device__ __forceinline__ void store_quad(float* __restrict__ p, f4v q, uint32_
 // a lower floor (two binades further down): the threshold lies there unless it
 // fell by more than that since the previous step, and then the level-1 select
 // rebuilds the block's full histogram itself.  The previous threshold is the
-// larger of the worker's own from its previous step and the same block's
-// latest at the preceding worker.
+// worker's own from its previous step or, in a call over a few workers, the
+// larger of that and the same block's latest at the preceding worker.
 //
 // With COLL, the previous step's global residual collection (Sec. III-C) is
 // applied to the tile before the gradient is added, in the order of the
