@@ -27,7 +27,7 @@ constexpr int SLOT = 4096;                       // elements per candidate slot 
 constexpr int MERGE_THREADS = 1024;               // a merge tile's serial steps (split search, merge,
 constexpr int MERGE_PER_THREAD = 4;                // histogram flush, bin sort) shrink with the positions per thread
 constexpr int MERGE_TILE = MERGE_THREADS * MERGE_PER_THREAD;   // merged positions per workgroup
-constexpr int DENSE_TILE = 8192;                 // output elements per densify workgroup (an LDS image)
+constexpr int DENSE_TILE = 4096;                 // output elements per densify workgroup (an LDS image)
 constexpr uint32_t HCOPIES_MIN = 4;               // level-1 histogram copies per block (spread the flush atomics)
 constexpr uint32_t HCOPIES_MAX = 32;
 

@@ -11,21 +11,48 @@ namespace spardl {
 // ============================================================================ a5: all-gather + densify
 // One workgroup per tile [t0, t0 + DENSE_TILE) of the output.  The tile is
 // built in LDS as an image -- zeros, then the final entries whose index falls
-// in the tile (both ends found by one joint search in the index-sorted final
-// blocks sp[b][b], whose loads overlap the image's zeroing) -- and written
-// once with whole-line stores, so no line of the output is written twice.
+// in the tile (each end found by one wave in the index-sorted final blocks
+// sp[b][b] while the others clear the image) -- and written once with
+// whole-line stores, so no line of the output is written twice.  Bound by the
+// chain search, entries, write against the workgroups that fit: 4096 elements
+// and 256 threads let eight share a CU.  For n = 25.6M, 138M, 110M: 30, 119 and
+// 91 us with 8192-element tiles and both searches by the whole workgroup, 27,
+// 96 and 83 with a wave per search, 22, 81 and 73 with 4096-element tiles (30,
+// 142 and 111 with 2048; 27, 125 and 100 with 512 threads); the write alone, at
+// 6.8 TB/s, is 15, 81 and 65.
 // With `member`, the tile's words of the membership bitmap of the final index
 // set I are written as well (bit x & 31 of word x >> 5 set iff x is in I),
 // every word of [0, ceil(n/32)) exactly once.
+constexpr int DENSE_THREADS = 256;
+
+// The first position of [lo, hi) whose entry is at or past x, found by one
+// wave, WAVE probes a round (a wider search fetches a line for every probe).
+__device__ __forceinline__ int32_t wave_lower_bound(const int32_t* __restrict__ F, int32_t lo, int32_t hi, int64_t x) {
+  const int lane = lane_id();
+  while (hi > lo) {   // uniform over the wave
+    const int32_t S = hi - lo;
+    const bool last = S <= WAVE;
+    const int32_t p = last ? min(lo + lane, hi - 1) : lo + (int32_t)(((int64_t)S * (lane + 1)) / (WAVE + 1));
+    const bool before = (!last || lane < S) && (int64_t)F[p] < x;
+    const int32_t c = (int32_t)popc64(__ballot(before));
+    if (last) return lo + c;
+    const int32_t nlo = c == 0 ? lo : lo + (int32_t)(((int64_t)S * c) / (WAVE + 1)) + 1;
+    const int32_t nhi = c == WAVE ? hi : lo + (int32_t)(((int64_t)S * (c + 1)) / (WAVE + 1));
+    lo = nlo;
+    hi = nhi;
+  }
+  return lo;
+}
+
 template <int VEC>
-__global__ __launch_bounds__(256) void k_densify(const int32_t* __restrict__ sp_idx,
+__global__ __launch_bounds__(DENSE_THREADS) void k_densify(const int32_t* __restrict__ sp_idx,
                                                  const float* __restrict__ sp_val, Blocks B,
                                                  int32_t kb, float* __restrict__ dense,
                                                  uint32_t* __restrict__ member) {
   static_assert(DENSE_TILE % 1024 == 0, "whole float4 rounds and bitmap words");
   __shared__ __align__(16) float img[DENSE_TILE];
   __shared__ uint32_t bits[DENSE_TILE / 32];
-  __shared__ uint32_t cnt[8];
+  __shared__ int32_t ends[2];
   const int64_t n = B.n;
   const int64_t t0 = (int64_t)blockIdx.x * DENSE_TILE;
   const int64_t t1 = min(t0 + DENSE_TILE, n);
@@ -36,10 +63,12 @@ __global__ __launch_bounds__(256) void k_densify(const int32_t* __restrict__ sp_
   for (uint32_t b = blo; b <= bhi; ++b) {
     const int32_t* Fi = sp_idx + ((int64_t)b * B.P + b) * kb;
     const float* Fv = sp_val + ((int64_t)b * B.P + b) * kb;
-    int32_t lo, hi;
-    wg_partition_point2(
-        0, kb, [&](int32_t p) { return (int64_t)Fi[p] < t0; }, 0, kb,
-        [&](int32_t p) { return (int64_t)Fi[p] < t1; }, cnt, &lo, &hi);   // its barriers order the zeroing
+    if (wave_id() < 2) {   // a wave per end
+      const int32_t at = wave_lower_bound(Fi, 0, kb, wave_id() == 0 ? t0 : t1);
+      if (lane_id() == 0) ends[wave_id()] = at;
+    }
+    __syncthreads();   // also orders the zeroing
+    const int32_t lo = ends[0], hi = ends[1];
     for (int32_t j = lo + (int32_t)threadIdx.x; j < hi; j += blockDim.x) {
       const int64_t r = (int64_t)Fi[j] - t0;
       if (r >= 0 && r < t1 - t0) {
@@ -47,8 +76,8 @@ __global__ __launch_bounds__(256) void k_densify(const int32_t* __restrict__ sp_
         atomicOr(&bits[r >> 5], 1u << (r & 31));
       }
     }
+    __syncthreads();   // the ends have been read
   }
-  __syncthreads();
   const int64_t len = t1 - t0;
   if (VEC == 4 && len == DENSE_TILE) {
     for (int i = threadIdx.x; i < DENSE_TILE / 4; i += blockDim.x)
@@ -216,8 +245,8 @@ hipError_t launch_densify(const int32_t* sp_idx, const float* sp_val, int32_t P,
                           float* dense, uint32_t* member, bool vec4, hipStream_t s) {
   const dim3 grid((unsigned)((n + DENSE_TILE - 1) / DENSE_TILE));
   const Blocks B = make_blocks(n, P);
-  if (vec4) hipLaunchKernelGGL(k_densify<4>, grid, dim3(256), 0, s, sp_idx, sp_val, B, kb, dense, member);
-  else hipLaunchKernelGGL(k_densify<1>, grid, dim3(256), 0, s, sp_idx, sp_val, B, kb, dense, member);
+  if (vec4) hipLaunchKernelGGL(k_densify<4>, grid, dim3(DENSE_THREADS), 0, s, sp_idx, sp_val, B, kb, dense, member);
+  else hipLaunchKernelGGL(k_densify<1>, grid, dim3(DENSE_THREADS), 0, s, sp_idx, sp_val, B, kb, dense, member);
   return hipGetLastError();
 }
 
