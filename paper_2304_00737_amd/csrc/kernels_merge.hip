@@ -297,7 +297,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_merge(
 // When a pair's union fits in LDS (merge_small in common.hpp), one workgroup
 // does the merge, the exact threshold and the emit of the tiled path in one
 // launch: both blocks are loaded into LDS, merged by merge-path splits
-// (SMALL_MP positions per thread; held first on equal indices, the held
+// (up to SMALL_MP positions per thread; held first on equal indices, the held
 // entry carrying held + received and the received one leaving a hole), the
 // union compacted in index order over the same LDS, its threshold found on
 // a fine level-1 histogram placed from the union's largest key and
@@ -306,8 +306,12 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_merge(
 // place, the rest into the step's drop list.  The held block is in LDS
 // before it is overwritten, and an SRS step never writes a block it
 // receives.  The results are the tiled path's: the same sums, selection rule
-// and orders.
-constexpr int SMALL_MP = SMALL_UNION / SMALL_THREADS;   // merged positions per thread
+// and orders.  Bound by the chain of barriers and one CU's issue, so a thread
+// takes no more positions than the union needs, and the emit writes runs (8
+// positions per thread whatever the union and 4-byte stores 32 bytes apart
+// took 11.7, 14.3 and 16.7 us for k_blk 164, 1250 and 2622; this 8.4, 12.2
+// and 15.8).
+constexpr int SMALL_MP = SMALL_UNION / SMALL_THREADS;   // most merged positions per thread
 
 __global__ __launch_bounds__(SMALL_THREADS) void k_merge_small(int32_t* __restrict__ sp_idx, float* __restrict__ sp_val,
                                                                Pairs PM, int32_t kb, int32_t* __restrict__ drop_idx,
@@ -318,12 +322,15 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_merge_small(int32_t* __restri
   __shared__ __align__(16) uint32_t h[NB1];
   __shared__ uint32_t scratch[3 * (SMALL_THREADS / WAVE) + 8];
   __shared__ uint32_t s_top;   // the union's largest key
+  constexpr uint32_t NWV = SMALL_THREADS / WAVE;
+  __shared__ uint32_t cw[SMALL_MP * NWV];   // emit: per (round, wave) the counts, then those before it
   const uint32_t unit = blockIdx.x;
   const int t = threadIdx.x;
   int64_t hb, rb;
   bool both;
   PM.decode(unit, &hb, &rb, &both);
   const int32_t L2 = 2 * kb;   // <= SMALL_UNION
+  const int32_t mp = (L2 + SMALL_THREADS - 1) / SMALL_THREADS;   // merged positions per thread
   {
     // held at [0, kb), received at [kb, 2 kb); every load first
     int32_t ti[SMALL_MP];
@@ -359,7 +366,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_merge_small(int32_t* __restri
   float ev[SMALL_MP];
   bool eok[SMALL_MP];
   uint32_t cnt = 0;
-  const int32_t q_lo = t * SMALL_MP;
+  const int32_t q_lo = t * mp;
   int32_t a = 0, bb = 0;
   if (q_lo < L2) {
     int32_t lo = max(0, q_lo - kb), hi = min(q_lo, kb);
@@ -376,7 +383,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_merge_small(int32_t* __restri
     eok[k] = false;
     ei[k] = 0;
     ev[k] = 0.f;
-    if (q_lo + k < L2) {
+    if (k < mp && q_lo + k < L2) {   // (k < mp: uniform)
       a = min(a, kb);     // only reachable with unsorted input; keeps LDS reads in range
       bb = min(bb, kb);
       const int32_t hx = hI(a), rx = rI(bb);
@@ -455,25 +462,37 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_merge_small(int32_t* __restri
                 }
               },
               tge, teq, need_eq);
-  // emit: each thread's SMALL_MP consecutive union entries, in index order
-  const uint32_t e0 = min((uint32_t)q_lo, tot), e1 = min(e0 + (uint32_t)SMALL_MP, tot);
-  uint32_t x3[3] = {0u, 0u, 0u}, t3[3];
-  for (uint32_t i = e0; i < e1; ++i) {
-    const uint32_t key = mag_key(sV[i]);
-    x3[0] += key >= tge ? 1u : 0u;
-    x3[1] += need_eq != 0u && key == teq ? 1u : 0u;
+  // emit in index order, a wave's 64 consecutive entries at a time: its selected
+  // ones and its drops each go to consecutive places
+  const int lane = lane_id(), wv = wave_id();
+  const uint64_t lt = __lanemask_lt();
+  const uint32_t rounds = (tot + (uint32_t)SMALL_THREADS - 1u) / (uint32_t)SMALL_THREADS;   // uniform
+  for (uint32_t r = 0; r < rounds; ++r) {
+    const uint32_t i = r * (uint32_t)SMALL_THREADS + (uint32_t)t;
+    const uint32_t key = i < tot ? mag_key(sV[i]) : 0u;
+    const uint32_t g = popc64(__ballot(i < tot && key >= tge));
+    const uint32_t q = popc64(__ballot(i < tot && need_eq != 0u && key == teq));
+    if (lane == 0) cw[r * NWV + (uint32_t)wv] = g | (q << 16);
   }
-  block_excl_scan3(x3, scratch, t3);
-  uint32_t run_g = x3[0], run_e = x3[1];
+  __syncthreads();
+  static_assert(SMALL_UNION < (1 << 16) && SMALL_MP * NWV <= SMALL_THREADS, "packed counts, one per thread");
+  uint32_t all;
+  const uint32_t before = block_excl_scan((uint32_t)t < rounds * NWV ? cw[t] : 0u, scratch, &all);
+  if ((uint32_t)t < rounds * NWV) cw[t] = before;
+  __syncthreads();
   const int64_t o = hb * kb, o2 = both ? rb * kb : -1;
-  for (uint32_t i = e0; i < e1; ++i) {
-    const int32_t ix = sI[i];
-    const float vx = sV[i];
+  for (uint32_t r = 0; r < rounds; ++r) {
+    const uint32_t i = r * (uint32_t)SMALL_THREADS + (uint32_t)t;
+    const int32_t ix = i < tot ? sI[i] : 0;
+    const float vx = i < tot ? sV[i] : 0.f;
     const uint32_t key = mag_key(vx);
-    const bool is_ge = key >= tge;
-    const bool is_eq = need_eq != 0u && key == teq;
-    const uint32_t sel_before = run_g + (run_e < need_eq ? run_e : need_eq);
-    if (is_ge || (is_eq && run_e < need_eq)) {
+    const bool is_ge = i < tot && key >= tge;
+    const bool is_eq = i < tot && need_eq != 0u && key == teq;
+    const uint64_t mg = __ballot(is_ge), me = __ballot(is_eq);
+    const uint32_t x = cw[r * NWV + (uint32_t)wv];
+    const uint32_t eq_before = (x >> 16) + popc64(me & lt);
+    const uint32_t sel_before = (x & 0xFFFFu) + popc64(mg & lt) + min(eq_before, need_eq);
+    if (is_ge || (is_eq && eq_before < need_eq)) {
       if (sel_before < (uint32_t)kb) {
         sp_idx[o + sel_before] = ix;
         sp_val[o + sel_before] = vx;
@@ -484,7 +503,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_merge_small(int32_t* __restri
       } else {
         atomicOr(err, ERR_COUNT_POS);
       }
-    } else {
+    } else if (i < tot) {
       const uint32_t dpos = i - sel_before;
       if (dpos < (uint32_t)kb) {
         drop_idx[(int64_t)unit * kb + dpos] = ix;
@@ -493,11 +512,9 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_merge_small(int32_t* __restri
         atomicOr(err, ERR_COUNT_DROP);
       }
     }
-    run_g += is_ge ? 1u : 0u;
-    run_e += is_eq ? 1u : 0u;
   }
   if (t == 0) {
-    if (t3[0] + (t3[1] < need_eq ? t3[1] : need_eq) != (uint32_t)kb) atomicOr(err, ERR_COUNT_SUM);
+    if ((all & 0xFFFFu) + min(all >> 16, need_eq) != (uint32_t)kb) atomicOr(err, ERR_COUNT_SUM);
     drop_cnt[unit] = (int32_t)(tot - (uint32_t)kb);
   }
 }
