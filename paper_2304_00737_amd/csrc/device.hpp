@@ -8,15 +8,15 @@ namespace spardl {
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // a float4 at any dword address
 
-// Adds the non-zero bins of an LDS histogram of NB1 bins into a global one,
+// Adds the non-zero bins of an LDS histogram of NB bins into a global one,
 // by a workgroup of NT threads.  Consecutive lanes take consecutive bins
 // (thread t bins t, t + NT, ...), so one wave's atomics fall on a few cache
 // lines (a lane-strided split multiplies the L2 atomic requests); a thread
 // issues all its LDS reads before its atomics.
-template <int NT>
+template <int NT, int NB = NB1>
 __device__ __forceinline__ void flush_hist(const uint32_t* h, uint32_t* __restrict__ H) {
-  constexpr int PER = NB1 / NT;
-  static_assert(PER * NT == NB1, "whole bins per thread");
+  constexpr int PER = NB / NT;
+  static_assert(PER * NT == NB, "whole bins per thread");
   uint32_t c[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) c[k] = h[threadIdx.x + k * NT];
@@ -47,13 +47,16 @@ __device__ __forceinline__ uint32_t hist_floor(uint32_t F) {
 // binades lower: the keys in [FH, F) in bins of the top 12 key bits (bins 0
 // .. M_MARGIN - 1), the keys from F up -- the speculative candidates, a few
 // per cent of the block -- in bins of 2^FINE_SHIFT keys (1/256 binade, bins
-// M_MARGIN .. NB1 - 1, the last also holding every larger key), so that a
-// threshold bin among the candidates holds few entries while a tile still
-// touches few bins.  Bin order is key order throughout.  Without a floor (a
+// M_MARGIN .. NB_FLOOR - 1, the last also holding every larger key), so that
+// a threshold bin among the candidates holds few entries while a tile still
+// touches few bins, and every tile clears and flushes, and the select sums,
+// NB_FLOOR of them (7.9 binades above F: a threshold that rises further in one
+// step has its block counted again).  Bin order is key order throughout.  Without a floor (a
 // block's first step, or a histogram made without the add) every key counts
 // and a bin is the top 12 key bits.  The fused add, the lazy receipts that
 // keep its histograms exact and the level-1 select all bin through this map.
 constexpr uint32_t M_MARGIN = HIST_MARGIN;   // 12-bit bins below the candidate floor
+constexpr int NB_FLOOR = NB1 / 2;            // bins of a histogram with a floor
 struct L1Map {
   uint32_t floor;   // smallest key counted (FH)
   uint32_t cand;    // the candidate floor F (fine bins from here)
@@ -61,7 +64,7 @@ struct L1Map {
   __device__ __forceinline__ uint32_t bin(uint32_t key) const {
     if (!fine) return key >> D1_SHIFT;
     if (key < cand) return (key >> D1_SHIFT) - (floor >> D1_SHIFT);   // key >= floor
-    return M_MARGIN + min((key >> FINE_SHIFT) - (cand >> FINE_SHIFT), (uint32_t)NB1 - 1u - M_MARGIN);
+    return M_MARGIN + min((key >> FINE_SHIFT) - (cand >> FINE_SHIFT), (uint32_t)NB_FLOOR - 1u - M_MARGIN);
   }
   // the keys of bin T: k >> *S == *pfx; false for the last fine bin, which
   // also holds every larger key
@@ -78,8 +81,9 @@ struct L1Map {
     }
     *pfx = (cand >> FINE_SHIFT) + (T - M_MARGIN);
     *S = FINE_SHIFT;
-    return T != (uint32_t)NB1 - 1u;
+    return T != (uint32_t)NB_FLOOR - 1u;
   }
+  __device__ __forceinline__ int bins() const { return fine ? NB_FLOOR : NB1; }
 };
 __device__ __forceinline__ L1Map l1_map(uint32_t used) {
   L1Map m;
@@ -88,7 +92,7 @@ __device__ __forceinline__ L1Map l1_map(uint32_t used) {
   m.floor = hist_floor(used);
   return m;
 }
-static_assert(HIST_MARGIN < (uint32_t)NB1 / 2, "the 12-bit margin bins leave most bins fine");
+static_assert(HIST_MARGIN < (uint32_t)NB_FLOOR / 2, "the 12-bit margin bins leave most bins fine");
 
 // Levels 2 and 3 over the keys of one level-1 bin, the keys k with
 // k >> S == pfx (visit(f) calls f(key) for each of them), in two digits of

@@ -290,9 +290,6 @@ __global__ __launch_bounds__(add_threads(COLL)) void k_residual_add4(float* __re
     }
     return;
   }
-  // the histogram is cleared while the loads are in flight (with COLL, a tile
-  // with drops clears its image's words again after the collection)
-  for (int i = threadIdx.x; i < NB1 / 4; i += NT) reinterpret_cast<uint4*>(h)[i] = make_uint4(0u, 0u, 0u, 0u);
   uint32_t F = SPEC_NONE;
   sw = max(sw, pw);
   if (sw != 0u) {
@@ -302,6 +299,10 @@ __global__ __launch_bounds__(add_threads(COLL)) void k_residual_add4(float* __re
   if (g == 0u && threadIdx.x == 0) sp.spec_used[wb] = F;
   const L1Map M = l1_map(F);
   const uint32_t FH = M.floor;
+  // the histogram is cleared while the loads are in flight (with COLL, a tile
+  // with drops clears its image's words again after the collection)
+  const int nz = COLL ? max(M.bins(), ADD_TILE) : M.bins();   // uniform
+  for (int i = threadIdx.x; i < nz / 4; i += NT) reinterpret_cast<uint4*>(h)[i] = make_uint4(0u, 0u, 0u, 0u);
   if constexpr (COLL) {
     // one thread turns the ranges into the tile's drop runs
     if (threadIdx.x == 0) {
@@ -440,7 +441,8 @@ __global__ __launch_bounds__(add_threads(COLL)) void k_residual_add4(float* __re
   }
   {
     uint32_t* __restrict__ H = sp.hist1 + ((int64_t)wb * sp.hcopies + (g & (sp.hcopies - 1u))) * NB1;   // a power of 2
-    flush_hist<NT>(h, H);
+    if (M.fine) flush_hist<NT, NB_FLOOR>(h, H);   // uniform
+    else flush_hist<NT>(h, H);
   }
   const uint32_t tot0 = tot & 0xFFFFu, all = tot0 + (tot >> 16);
   const uint32_t ex = base + incl - packed;

@@ -16,6 +16,7 @@
 #include "launch.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace spardl {
 
@@ -43,32 +44,37 @@ template <int NT, bool CLEAR>
 __device__ __forceinline__ Level1 block_level1(uint32_t* __restrict__ H, uint32_t hc, uint32_t used, uint32_t need,
                                                const float* __restrict__ A, uint32_t s, uint32_t e, bool may_recount,
                                                bool report, uint32_t* h, uint32_t* scratch, uint32_t* __restrict__ err) {
-  constexpr int PER = NB1 / NT;
   static_assert(HCOPIES_MIN == 4, "copies are summed four at a time");
-  uint32_t c[PER];
-#pragma unroll
-  for (int q = 0; q < PER; ++q) c[q] = 0u;
-  for (uint32_t k0 = 0; k0 < hc; k0 += HCOPIES_MIN) {
-    uint32_t r[PER][HCOPIES_MIN];
-#pragma unroll
-    for (int q = 0; q < PER; ++q)
-#pragma unroll
-      for (uint32_t k = 0; k < HCOPIES_MIN; ++k) r[q][k] = H[(k0 + k) * NB1 + q * NT + threadIdx.x];
-#pragma unroll
-    for (int q = 0; q < PER; ++q)
-#pragma unroll
-      for (uint32_t k = 0; k < HCOPIES_MIN; ++k) {
-        c[q] += r[q][k];
-        if (CLEAR) H[(k0 + k) * NB1 + q * NT + threadIdx.x] = 0u;
-      }
-  }
-#pragma unroll
-  for (int q = 0; q < PER; ++q) h[q * NT + threadIdx.x] = c[q];
   const L1Map M = l1_map(used);
+  const int nb = M.bins();   // uniform
+  auto sum_copies = [&](auto bins) {
+    constexpr int PER = decltype(bins)::value / NT;
+    uint32_t c[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) c[q] = 0u;
+    for (uint32_t k0 = 0; k0 < hc; k0 += HCOPIES_MIN) {
+      uint32_t r[PER][HCOPIES_MIN];
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+#pragma unroll
+        for (uint32_t k = 0; k < HCOPIES_MIN; ++k) r[q][k] = H[(k0 + k) * NB1 + q * NT + threadIdx.x];
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+#pragma unroll
+        for (uint32_t k = 0; k < HCOPIES_MIN; ++k) {
+          c[q] += r[q][k];
+          if (CLEAR) H[(k0 + k) * NB1 + q * NT + threadIdx.x] = 0u;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) h[q * NT + threadIdx.x] = c[q];
+  };
+  if (M.fine) sum_copies(std::integral_constant<int, NB_FLOOR>{});
+  else sum_copies(std::integral_constant<int, NB1>{});
   __syncthreads();
   Level1 R;
   uint32_t T, total;
-  block_select_desc(h, NB1, need, scratch, &T, &R.above, &R.cnt, &R.ok, &total);
+  block_select_desc(h, nb, need, scratch, &T, &R.above, &R.cnt, &R.ok, &total);
   bool full = !M.fine;   // the top-12-bit histogram of every key
   R.pfx = T;
   R.S = D1_SHIFT;
@@ -329,7 +335,7 @@ __device__ __forceinline__ void collect_slots(const float* __restrict__ A, uint3
 // before any of its writes, and a compacted position never exceeds the
 // storage position of an entry not yet read, so no barrier is needed.
 static_assert(SLOT == 2 * ADD_TILE, "a slot holds two residual-add tiles");
-constexpr int RC_R = 16;  // entries per lane per chunk (a crowded slot holds up to 4096)
+constexpr int RC_R = 8;   // entries per lane per chunk (a crowded slot holds up to 4096; with 16 most registers are walked for nothing)
 __device__ __forceinline__ void recollect_wave(uint32_t c0, uint32_t c1, uint32_t off1, uint32_t tlo, uint32_t thi,
                                                uint32_t* cnt_out, uint32_t* nbin_out, int32_t* __restrict__ CI,
                                                float* __restrict__ CV, uint32_t* __restrict__ BK) {
@@ -1507,9 +1513,9 @@ __global__ __launch_bounds__(1024) void k_big_scan(BigArgs a) {
 // and each wave a quarter of it, the counts of the quarters before it
 // exchanged through LDS; selected -> sp[w][b] in place, the rest -> the
 // step's drop lists.
-constexpr int EMIT_R = 16;    // entries per lane per chunk (a crowded slot holds up to 4096)
+constexpr int EMIT_R = 16;    // merge: entries per lane, a quarter of a slot
 constexpr int EMIT_R1 = 4;    // block top-k, several slots per wave: first entries per lane of each slot
-constexpr int EMIT_R0 = 8;    // ... entries per lane per chunk after the first
+constexpr int EMIT_R0 = 8;    // block top-k: entries per lane per chunk (of several slots: after the first)
 
 // Block top-k emit of one slot whose first R1 WAVE entries are in ix1 / vx1
 // (lane l holds entries r WAVE + l); run_g / run_e: the >= and == counts of
@@ -1600,11 +1606,11 @@ __global__ __launch_bounds__(256) void k_emit(
       kp[KEEP_TEQ] = teq;
       kp[KEEP_NEEDEQ] = need_eq;
     }
-    for (uint32_t e0 = 0; e0 < cnt; e0 += WAVE * EMIT_R) {
-      int32_t ix[EMIT_R];
-      float vx[EMIT_R];
+    for (uint32_t e0 = 0; e0 < cnt; e0 += WAVE * EMIT_R0) {
+      int32_t ix[EMIT_R0];
+      float vx[EMIT_R0];
 #pragma unroll
-      for (int r = 0; r < EMIT_R; ++r) {
+      for (int r = 0; r < EMIT_R0; ++r) {
         const uint32_t p = e0 + r * WAVE + lane;
         ix[r] = -1;
         vx[r] = 0.f;
@@ -1614,7 +1620,7 @@ __global__ __launch_bounds__(256) void k_emit(
         }
       }
 #pragma unroll
-      for (int r = 0; r < EMIT_R; ++r) {
+      for (int r = 0; r < EMIT_R0; ++r) {
         const uint32_t p = e0 + r * WAVE + lane;
         const uint32_t key = mag_key(vx[r]);
         const bool is_ge = p < cnt && key >= tge;
@@ -2017,7 +2023,10 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
   __syncthreads();
   // the histogram copies rest at zero between steps (cleared here, behind the
   // loads: a load issued after stores is waited for with them)
-  for (uint32_t i = t; i < a.hc * (uint32_t)(NB1 / 4); i += ONE_THREADS) reinterpret_cast<uint4*>(H)[i] = make_uint4(0u, 0u, 0u, 0u);
+  const uint32_t nb4 = (uint32_t)l1_map(used).bins() / 4u;   // of each copy
+  static_assert(NB1 / 4 == ONE_THREADS, "one uint4 of a copy per thread");
+  if (t < nb4)
+    for (uint32_t k = 0; k < a.hc; ++k) reinterpret_cast<uint4*>(H + k * NB1)[t] = make_uint4(0u, 0u, 0u, 0u);
   uint32_t T, above, cnt, ok;
   block_select_desc(h, NB1, a.kb, scratch, &T, &above, &cnt, &ok);
   int S = FINE_SHIFT;

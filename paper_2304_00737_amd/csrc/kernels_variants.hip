@@ -439,10 +439,11 @@ __global__ __launch_bounds__(256) void k_lazy_step(float* __restrict__ acc, int6
       const int64_t cu = (int64_t)r * B.P + b;   // the receiver block's arrays
       const L1Map M = l1_map(spec_used[cu]);   // the add's bins
       const uint32_t FH = M.floor;
+      const int nb = M.bins();
       const uint32_t j0 = blockIdx.x * LAZY_CHUNK;
       if (j0 >= kb) continue;
       if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&spec_used[cu], SPEC_DIRTY);
-      for (int i = threadIdx.x; i < NB1; i += 256) dh[i] = 0u;
+      for (int i = threadIdx.x; i < nb; i += 256) dh[i] = 0u;
       __syncthreads();
       // the chunk's entries, then the values they land on, all loads in flight
       // before any store (a pair's indices are distinct, so no entry's store
@@ -479,7 +480,7 @@ __global__ __launch_bounds__(256) void k_lazy_step(float* __restrict__ acc, int6
       }
       __syncthreads();
       uint32_t* __restrict__ H = hist1 + (cu * hc + (blockIdx.x % HCOPIES_MIN)) * NB1;
-      for (int i = threadIdx.x; i < NB1; i += 256) {
+      for (int i = threadIdx.x; i < nb; i += 256) {
         const uint32_t c = dh[i];   // a signed delta, added modulo 2^32
         if (c) atomicAdd(&H[i], c);
       }
