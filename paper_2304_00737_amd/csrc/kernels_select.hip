@@ -1803,12 +1803,13 @@ __global__ __launch_bounds__(256) void k_emit(
 // ============================================================================ a3 in one workgroup per block
 // A block that selects few entries (topk_one below) has its candidates in one
 // workgroup's registers: the fused add's, when they hold the whole selection
-// (at least `need` keys at or above the floor), else those the block's own
-// level-1 threshold leaves.  One launch then finds the exact threshold and
+// (at least `need` keys at or above the floor) and fit, else those the block's
+// own level-1 threshold leaves.  One launch then finds the exact threshold and
 // writes the selection, where the general path takes four dependent ones, each
 // mostly waiting; what it writes is the same.  A block the candidates do not
-// decide (its first step, a fallen threshold, entries changed since the add) is
-// first reduced to them: by k_one_prep, with workgroups enough to stream it,
+// decide (its first step, a fallen threshold, entries changed since the add, or
+// more candidates than the registers hold, as a residual that piles up below
+// the threshold leaves) is first reduced to them: by k_one_prep, with workgroups enough to stream it,
 // or, up to ONE_SELF elements, by the same workgroup.  It is bound by the
 // chain of barriers and by one CU's instruction issue (a tile list's search, 7
 // to 10 LDS reads, is most of it), which is why it ends at ONE_KB entries.  The
@@ -1850,6 +1851,8 @@ __device__ __forceinline__ uint32_t tiles_of(uint32_t s, uint32_t e) {
 }
 // Whether a block with this word of the add has candidates at all.
 __device__ __forceinline__ bool spec_valid(uint32_t used) { return used != SPEC_NONE && !(used & SPEC_DIRTY); }
+// Whether N candidates decide a block that selects kb.
+__device__ __forceinline__ bool spec_decides(uint32_t N, uint32_t kb) { return N >= kb && N <= (uint32_t)ONE_CAP; }
 
 // The blocks their candidates do not decide: level-1 threshold, then the
 // block's entries at or above its bin into its slots, PREP_SLOTS per
@@ -1869,7 +1872,7 @@ __global__ __launch_bounds__(256) void k_one_prep(TopkOne a, uint32_t gq) {
     const uint32_t nt = tiles_of(s, e);
     for (uint32_t g = threadIdx.x; g < nt; g += 256u) c += tile_candidates(a, u, s, e, g);
     block_excl_scan(c, scratch, &total);
-    if (total >= a.kb) return;   // uniform
+    if (spec_decides(total, a.kb)) return;   // uniform
   }
   const uint32_t slot0 = (blockIdx.x % gq) * PREP_SLOTS;
   if (block_origin(s) + slot0 * (uint32_t)SLOT >= e) return;
@@ -1922,7 +1925,7 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
   const bool valid = spec_valid(used);   // uniform
   if (!valid) c0 = 0u;
   uint32_t ex = block_excl_scan(c0, scratch, &N);
-  const bool specok = valid && N >= a.kb;   // uniform
+  const bool specok = valid && spec_decides(N, a.kb);   // uniform
   if (!specok && a.self) {
     const float* __restrict__ A = a.acc + (int64_t)w * a.ld_acc;
     const Level1 R = block_level1<ONE_THREADS, false>(H, a.hc, used, a.kb, A, s, e, true, true, h, scratch, a.err);

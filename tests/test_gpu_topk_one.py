@@ -64,3 +64,23 @@ def test_topk_one_lazy(P, n, kb):
         check_ws(st)
         res = so.spardl_step_lazy([acc[w] for w in range(P)], [grad[w] for w in range(P)], P, n, kb)
         compare_lazy_step(st, res, P, n, kb)
+
+
+# blocks of 16384 elements (all of them fit), 65536 (the workgroup streams them), 65537 and 2^18 (the launch before it)
+@pytest.mark.parametrize("P,n,kb", [(4, 4 * 16384, 300), (4, 4 * 65536, 4096), (2, 2 * 65537, 300), (4, 1 << 20, 2622)])
+def test_topk_one_piled_up(P, n, kb):
+    """A residual piled up just below the threshold: a third, then all of a
+    block within the candidates' margin, on both sides of what the registers hold."""
+    st = spardl.SparDLStep(P, n, kb, fuse_collect=True)
+    acc = np.zeros((P, n), np.float32)
+    rng = np.random.default_rng(n)
+    for t in range(6):
+        log(f"topk in one workgroup, piled up P={P} n={n} kb={kb} step {t + 1}")
+        grad = np.float32(1e-3) * rng.standard_normal((P, n)).astype(np.float32)
+        if t in (0, 3):
+            some = rng.random((P, n)) < (0.33 if t == 0 else 1.0)
+            grad[some] = (rng.choice([-1.0, 1.0], n * P) * rng.uniform(1.0, 1.05, n * P)).astype(np.float32).reshape(P, n)[some]
+        st.step(torch.from_numpy(grad).cuda())
+        check_ws(st)
+        res = so.spardl_step([acc[w] for w in range(P)], [grad[w] for w in range(P)], P, n, kb)
+        compare_step(st, res, P, n, kb, residual=False)
