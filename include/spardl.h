@@ -150,9 +150,9 @@ int spardl_residual_add(float* acc, int64_t ld_acc, const float* grad, int64_t l
  * them and as for spardl_residual_collect (the decode's bitmap; HOST arrays
  * of l DEVICE pointers, element i-1 the buffers of SRS step i for all P
  * workers; they may be NULL when P = 1).  acc, grad, local_idx: the rows
- * w0 .. w0 + nworkers - 1 (local_idx as spardl_block_topk wrote it; read
- * only for rows the float4 add does not take, which are collected by the
- * separate kernels before the add).  The drops are read through a per-tile
+ * w0 .. w0 + nworkers - 1 (local_idx as spardl_block_topk wrote it: large
+ * sparse steps, and P > 65536, are collected by the separate kernels before
+ * the add, which read it).  The drops are read through a per-tile
  * index that spardl_residual_collect_index must have built in ws after the
  * previous step's SRS steps, for these rows and these drop lists.
  * Errors: as for spardl_residual_add with ws, plus EINVAL for NULL
@@ -173,8 +173,8 @@ int spardl_residual_add_collect(float* acc, int64_t ld_acc, const float* grad, i
  * drop_cnt too) and adds only entries inside its tile, so a range a tile
  * kept from an earlier step adds nothing.  drop_idx / drop_cnt: HOST
  * arrays of l DEVICE pointers, as for spardl_residual_collect.  Nothing is
- * enqueued where the add collects without an index (P = 1, P > 256, or
- * blocks not float4-aligned).
+ * enqueued where the add collects without an index (P = 1, P > 65536, or large
+ * sparse steps, which the separate kernels collect).
  * The index lives in the part of the workspace that does not grow with its
  * rows, so any workspace for these sizes holds it (a workspace for fewer
  * rows than P included).

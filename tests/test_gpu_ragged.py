@@ -66,3 +66,28 @@ def test_plain_add_many_rows():
     want = a + g
     spardl.residual_add(a, g, 70000, 3)
     assert torch.equal(a, want)
+
+
+@pytest.mark.parametrize("rows", [0, 1])
+@pytest.mark.parametrize("n,kb", [(2 ** 26, 1000), (2 ** 26 - 1, 1000), (2 ** 26 + 3, 1000),
+                                  (2 ** 26, 2 ** 19), (2 ** 26, 2 ** 19 + 1)])
+def test_collection_in_the_add_or_before_it(n, kb, rows):
+    """Both sides of the sizes and densities where the deferred collection
+    moves between the add's tiles and kernels before it: the same steps as
+    with the collection as its own call."""
+    P = 2
+    log(f"collection in the add or before it n={n} kb={kb} rows={rows}")
+    deferred = spardl.SparDLStep(P, n, kb, rows_per_call=rows, fuse_collect=True)
+    own = spardl.SparDLStep(P, n, kb, rows_per_call=rows)
+    gen = torch.Generator(device="cuda").manual_seed(n + kb)
+    grad = torch.empty((P, n), device="cuda")
+    for t in range(3):
+        grad.normal_(generator=gen)
+        for st in (deferred, own):
+            st.step(grad)
+            check_ws(st)
+        assert torch.equal(deferred.dense, own.dense), f"update of step {t + 1}"
+        assert torch.equal(deferred.local_idx, own.local_idx), f"selections of step {t + 1}"
+    deferred.flush()
+    check_ws(deferred)
+    assert torch.equal(deferred.acc.view(torch.int32), own.acc.view(torch.int32)), "residual"
