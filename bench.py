@@ -319,9 +319,9 @@ def main() -> int:
                           / args.steps - marker_ms, 0.0) for ci, c in enumerate(calls)}
 
     # ---- dominant kernel: the residual add is one kernel per call (with the
-    # previous step's collection fused in; its drop index is built by the
-    # collect call); each launch is bracketed by an event pair on its stream
-    # (marker cost removed)
+    # previous step's collection in its tiles, its drop index built by the
+    # collect call, or in kernels of the same call before it); each call is
+    # bracketed by an event pair on its stream (marker cost removed)
     g0 = grads[0]
     k_mid = [(ev(), ev()) for _ in range(args.steps)]
     for j in range(args.steps):
@@ -445,7 +445,8 @@ def main() -> int:
                    "L_per_team_block": st.k_blk if d > 1 else None,
                    "residual_collection": ("inside the next step's residual add" if getattr(st, "fuse_collect", False)
                                            else "its own call at the end of the step")},
-        "roofline": {"bound": "hbm", "kernel": (("k_residual_add4<true, true> (the previous step's collection fused in)"
+        "roofline": {"bound": "hbm", "kernel": (("k_residual_add4 (the previous step's collection in its tiles or, by size and "
+                                                  "density, in kernels of the same call before it)"
                                                   if getattr(st, "fuse_collect", False) else "k_residual_add4<true, false>")
                                                  if dominant == "residual_add" else dominant),
                      "achieved": achieved, "peak": HBM_PEAK_GBS,
@@ -640,7 +641,8 @@ def per_worker_measure(wl, dev, steps: int, warmup: int, R: int, lazy: bool, fus
                    "timing": "ms_per_step: sum of the event-timed hot calls; span_ms_per_step: the whole step's "
                              "span on the stream less the gradient generation inside it; the workers' gradients "
                              f"are generated on the GPU between their calls, {R} rows per call ({R}-row workspace)"},
-        "roofline": {"bound": "hbm", "kernel": ("k_residual_add4<true, true> (the previous step's collection fused in)"
+        "roofline": {"bound": "hbm", "kernel": ("k_residual_add4 (the previous step's collection in its tiles or, by size and "
+                                                "density, in kernels of the same call before it)"
                                                 if getattr(st, "fuse_collect", False) else "k_residual_add4<true, false>"),
                      "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
