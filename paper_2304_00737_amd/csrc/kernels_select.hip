@@ -1822,7 +1822,10 @@ constexpr int ONE_CAP = ONE_THREADS * ONE_R;         // a chunk; further chunks 
 constexpr int ONE_LISTS = ONE_THREADS;               // most add tiles per block: a list per thread
 constexpr int ONE_KB = 4096;                         // most entries selected (staged in LDS)
 constexpr int64_t ONE_SELF = 1 << 16;
-constexpr uint32_t PREP_SLOTS = 8;                   // slots per workgroup of k_one_prep
+constexpr uint32_t PREP_SLOTS = 8;                   // most slots per workgroup of k_one_prep
+// ... fewer while that makes fewer workgroups than this: 16 piled-up blocks of 2^18 took 15 us with eight slots
+// each (128 workgroups, half the CUs), 8 with two.
+constexpr int64_t PREP_GROUPS = 512;
 
 struct TopkOne {
   const float* acc;
@@ -1855,10 +1858,10 @@ __device__ __forceinline__ bool spec_valid(uint32_t used) { return used != SPEC_
 __device__ __forceinline__ bool spec_decides(uint32_t N, uint32_t kb) { return N >= kb && N <= (uint32_t)ONE_CAP; }
 
 // The blocks their candidates do not decide: level-1 threshold, then the
-// block's entries at or above its bin into its slots, PREP_SLOTS per
+// block's entries at or above its bin into its slots, `per` of them per
 // workgroup.  Every workgroup of a block finds the threshold itself; a block
 // that has to be counted again is left to its first one.
-__global__ __launch_bounds__(256) void k_one_prep(TopkOne a, uint32_t gq) {
+__global__ __launch_bounds__(256) void k_one_prep(TopkOne a, uint32_t gq, uint32_t per) {
   __shared__ uint32_t h[NB1];
   __shared__ CollectSmem L;
   __shared__ uint32_t scratch[16];
@@ -1874,13 +1877,13 @@ __global__ __launch_bounds__(256) void k_one_prep(TopkOne a, uint32_t gq) {
     block_excl_scan(c, scratch, &total);
     if (spec_decides(total, a.kb)) return;   // uniform
   }
-  const uint32_t slot0 = (blockIdx.x % gq) * PREP_SLOTS;
+  const uint32_t slot0 = (blockIdx.x % gq) * per;
   if (block_origin(s) + slot0 * (uint32_t)SLOT >= e) return;
   const float* __restrict__ A = a.acc + (int64_t)w * a.ld_acc;
   // counted again only by the first workgroup, which then takes the whole block
   Level1 R = block_level1<256, false>(a.hist1 + u * a.hc * NB1, a.hc, used, a.kb, A, s, e, false, slot0 == 0u, h, scratch,
                                      a.err);
-  uint32_t count = PREP_SLOTS;
+  uint32_t count = per;
   if (!R.ok) {   // uniform
     if (slot0 != 0u) return;
     __syncthreads();
@@ -2159,8 +2162,9 @@ hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, con
   a.local_idx = local_idx;
   a.out_val = out_val;
   if (!a.self) {
-    const uint32_t gq = ((uint32_t)smax + PREP_SLOTS - 1u) / PREP_SLOTS;
-    hipLaunchKernelGGL(k_one_prep, dim3((unsigned)(nunits * gq)), dim3(256), 0, s, a, gq);
+    const uint32_t per = (uint32_t)std::clamp<int64_t>(nunits * smax / PREP_GROUPS, 1, PREP_SLOTS);
+    const uint32_t gq = ((uint32_t)smax + per - 1u) / per;
+    hipLaunchKernelGGL(k_one_prep, dim3((unsigned)(nunits * gq)), dim3(256), 0, s, a, gq, per);
   }
   hipLaunchKernelGGL(k_topk_one, dim3((unsigned)nunits), dim3(ONE_THREADS), 0, s, a);
   return hipGetLastError();
