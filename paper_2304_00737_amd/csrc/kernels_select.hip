@@ -87,26 +87,28 @@ __device__ __forceinline__ Level1 block_level1(uint32_t* __restrict__ H, uint32_
     }
     for (int i = threadIdx.x; i < NB1; i += NT) h[i] = 0u;
     __syncthreads();
-    for (uint32_t x0 = s + threadIdx.x * 4u; x0 < e; x0 += NT * 4u * 4u) {
+    // (whole float4 first and the rest after them: a branch to single elements beside the loads keeps
+    // the four from being in flight together, 689 against 530 us for 64 blocks of 3.2M)
+    const uint32_t e4 = e - ((e - s) & 3u);
+    for (uint32_t x0 = s + threadIdx.x * 4u; x0 < e4; x0 += NT * 4u * 4u) {
       f4v v[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const uint32_t x = x0 + (uint32_t)k * NT * 4u;
-        if (x < e && e - x >= 4u) v[k] = *reinterpret_cast<const f4u*>(A + x);
+        if (x < e4) v[k] = *reinterpret_cast<const f4u*>(A + x);
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const uint32_t x = x0 + (uint32_t)k * NT * 4u;
-        if (x < e && e - x >= 4u) {
+        if (x < e4) {
           atomicAdd(&h[mag_key(v[k].x) >> D1_SHIFT], 1u);
           atomicAdd(&h[mag_key(v[k].y) >> D1_SHIFT], 1u);
           atomicAdd(&h[mag_key(v[k].z) >> D1_SHIFT], 1u);
           atomicAdd(&h[mag_key(v[k].w) >> D1_SHIFT], 1u);
-        } else if (x < e) {   // the block's last elements
-          for (uint32_t y = x; y < e; ++y) atomicAdd(&h[mag_key(A[y]) >> D1_SHIFT], 1u);
         }
       }
     }
+    if (threadIdx.x < e - e4) atomicAdd(&h[mag_key(A[e4 + threadIdx.x]) >> D1_SHIFT], 1u);
     __syncthreads();
     block_select_desc(h, NB1, need, scratch, &T, &R.above, &R.cnt, &R.ok, &total);
     full = true;
