@@ -292,17 +292,20 @@ int topk_units(const float* acc, int64_t ld_acc, int64_t units, const Units& U, 
   // lazy selection that did not start from a fused add; hint_off: the words of
   // the workers before the call's rows (hints are kept per absolute worker)
   uint32_t* hint = (U.rel && !spec) ? nullptr : w.spec_t1 + hint_off;
-  if (topk_one(k_blk, L.add_tiles)) {
+  const bool one = topk_one(k_blk, L.add_tiles);
+  if (!one || !topk_alone(n, P)) {
+    SPARDL_TRY(launch_select1(w.hist1, w.state, units, U, n, P, (uint32_t)k_blk, hint, w.spec_used, spec, acc, ld_acc,
+                              smax, one, w.err, stream));
+    SPARDL_TRY(launch_collect(acc, ld_acc, units, U, n, P, k_blk, smax, w.state, w.spec_cnt, (int32_t)L.add_tiles,
+                              w.slot_cnt, w.slot_nbin, w.cand_idx, w.cand_val, w.bin_key, stream));
+  }
+  if (one) {
     SPARDL_TRY(launch_topk_one(acc, ld_acc, units, U, n, P, k_blk, smax, (int32_t)L.add_tiles, spec, w.hist1, w.state,
                                hint, w.spec_used, w.spec_cnt, w.slot_cnt, w.slot_nbin, w.cand_idx, w.cand_val, w.bin_key,
                                sp_idx, sp_val, local_idx, keep_rule ? w.keep + hint_off * KEEP_WORDS : nullptr, w.err,
                                stream));
     return SPARDL_OK;
   }
-  SPARDL_TRY(launch_select1(w.hist1, w.state, units, U, n, P, (uint32_t)k_blk, hint, w.spec_used, spec, acc, ld_acc,
-                            w.err, stream));
-  SPARDL_TRY(launch_collect(acc, ld_acc, units, U, n, P, k_blk, smax, w.state, w.spec_cnt, (int32_t)L.add_tiles,
-                            w.slot_cnt, w.slot_nbin, w.cand_idx, w.cand_val, w.bin_key, stream));
   // hist1: the staged threshold for long units builds its level-2/3 histograms in the units'
   // level-1 histogram space, which the select has cleared
   SPARDL_TRY(launch_thresh(0, units, U, n, P, k_blk, smax, w.hist1, w.cand_val, w.state, w.slot_cnt,

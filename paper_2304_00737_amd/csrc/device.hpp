@@ -94,16 +94,30 @@ __device__ __forceinline__ L1Map l1_map(uint32_t used) {
 }
 static_assert(HIST_MARGIN < (uint32_t)NB_FLOOR / 2, "the 12-bit margin bins leave most bins fine");
 
+// Adds one to word i of an LDS histogram.  `same` (uniform): the lanes mostly
+// agree on i; those that agree with the first one then add once for all of
+// them, where the LDS would take them one after another.
+__device__ __forceinline__ void hist_add(uint32_t* h, uint32_t i, bool same) {
+  if (!same) {
+    atomicAdd(&h[i], 1u);
+    return;
+  }
+  const uint32_t i0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)i);
+  const uint64_t m = __ballot(i == i0);   // of the active lanes
+  if (i != i0) atomicAdd(&h[i], 1u);
+  else if ((m & __lanemask_lt()) == 0u) atomicAdd(&h[i0], popc64(m));
+}
+
 // Levels 2 and 3 over the keys of one level-1 bin, the keys k with
 // k >> S == pfx (visit(f) calls f(key) for each of them), in two digits of
 // the low S bits, the last of S == FINE_SHIFT ? 7 : 8 bits; h holds at
 // least 2^(S - that) words.  Returns the threshold as (tge, teq, need_eq):
 // every key >= tge is selected, and the first need_eq (by index) with key
-// == teq.
+// == teq.  same: as for hist_add.
 template <typename Visit>
 __device__ __forceinline__ void resolve_bin(uint32_t pfx, int S, uint32_t need1, uint32_t cnt1, uint32_t* h,
                                             uint32_t* scratch, uint32_t* err, Visit visit, uint32_t& tge,
-                                            uint32_t& teq, uint32_t& need_eq) {
+                                            uint32_t& teq, uint32_t& need_eq, bool same = false) {
   const int D3 = S == FINE_SHIFT ? 7 : 8;
   const int nb2 = 1 << (S - D3), nb3 = 1 << D3;
   tge = pfx << S;
@@ -113,7 +127,7 @@ __device__ __forceinline__ void resolve_bin(uint32_t pfx, int S, uint32_t need1,
   __syncthreads();
   for (int i = threadIdx.x; i < nb2; i += blockDim.x) h[i] = 0u;
   __syncthreads();
-  visit([&](uint32_t key) { atomicAdd(&h[(key >> D3) & (uint32_t)(nb2 - 1)], 1u); });
+  visit([&](uint32_t key) { hist_add(h, (key >> D3) & (uint32_t)(nb2 - 1), same); });
   __syncthreads();
   uint32_t T2, above2, cnt2, ok;
   block_select_desc(h, nb2, need1, scratch, &T2, &above2, &cnt2, &ok);
@@ -128,7 +142,7 @@ __device__ __forceinline__ void resolve_bin(uint32_t pfx, int S, uint32_t need1,
   for (int i = threadIdx.x; i < nb3; i += blockDim.x) h[i] = 0u;
   __syncthreads();
   visit([&](uint32_t key) {
-    if ((key >> D3) == pre) atomicAdd(&h[key & (uint32_t)(nb3 - 1)], 1u);
+    if ((key >> D3) == pre) hist_add(h, key & (uint32_t)(nb3 - 1), same);
   });
   __syncthreads();
   uint32_t T3, above3, cnt3;

@@ -34,16 +34,15 @@ struct Level1 {
   uint32_t pfx, S;      // the threshold bin: the keys k with k >> S == pfx
   uint32_t above, cnt;  // entries above the bin, and in it
   uint32_t ok;          // 0: no threshold found
+  bool full;            // h holds the block's top 12 key bits (else the add's bins)
 };
 
 // By a workgroup of NT threads (every thread gets the answer); h: NB1 words of
 // LDS, scratch: NT / WAVE + 4.  H: the block's hc copies, cleared if CLEAR.
-// may_recount: if false, ok = 0 where the block has to be counted from acc.
-// report: whether a histogram that cannot be the block's sets the error word.
 template <int NT, bool CLEAR>
 __device__ __forceinline__ Level1 block_level1(uint32_t* __restrict__ H, uint32_t hc, uint32_t used, uint32_t need,
-                                               const float* __restrict__ A, uint32_t s, uint32_t e, bool may_recount,
-                                               bool report, uint32_t* h, uint32_t* scratch, uint32_t* __restrict__ err) {
+                                               const float* __restrict__ A, uint32_t s, uint32_t e, uint32_t* h,
+                                               uint32_t* scratch, uint32_t* __restrict__ err) {
   static_assert(HCOPIES_MIN == 4, "copies are summed four at a time");
   const L1Map M = l1_map(used);
   const int nb = M.bins();   // uniform
@@ -75,16 +74,12 @@ __device__ __forceinline__ Level1 block_level1(uint32_t* __restrict__ H, uint32_
   Level1 R;
   uint32_t T, total;
   block_select_desc(h, nb, need, scratch, &T, &R.above, &R.cnt, &R.ok, &total);
-  bool full = !M.fine;   // the top-12-bit histogram of every key
+  R.full = !M.fine;   // the top-12-bit histogram of every key
   R.pfx = T;
   R.S = D1_SHIFT;
   // the threshold fell below the histogram's floor, or above its fine window:
   // count the whole block by its top 12 key bits
-  if (!full && (!R.ok || !M.bin_keys(T, &R.pfx, &R.S))) {
-    if (!may_recount) {
-      R.ok = 0u;
-      return R;
-    }
+  if (!R.full && (!R.ok || !M.bin_keys(T, &R.pfx, &R.S))) {
     for (int i = threadIdx.x; i < NB1; i += NT) h[i] = 0u;
     __syncthreads();
     // (whole float4 first and the rest after them: a branch to single elements beside the loads keeps
@@ -111,12 +106,12 @@ __device__ __forceinline__ Level1 block_level1(uint32_t* __restrict__ H, uint32_
     if (threadIdx.x < e - e4) atomicAdd(&h[mag_key(A[e4 + threadIdx.x]) >> D1_SHIFT], 1u);
     __syncthreads();
     block_select_desc(h, NB1, need, scratch, &T, &R.above, &R.cnt, &R.ok, &total);
-    full = true;
+    R.full = true;
     R.pfx = T;
     R.S = D1_SHIFT;
   }
   const uint32_t len = e - s;
-  if (threadIdx.x == 0 && report && (!R.ok || (full ? total != len : total > len))) atomicOr(err, ERR_COUNT);
+  if (threadIdx.x == 0 && (!R.ok || (R.full ? total != len : total > len))) atomicOr(err, ERR_COUNT);
   return R;
 }
 
@@ -124,7 +119,7 @@ __global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, 
                                                   Blocks B, Units U, uint32_t need, uint32_t* __restrict__ spec_t1,
                                                   const uint32_t* __restrict__ spec_used, int spec,
                                                   const float* __restrict__ acc, int64_t ld_acc,
-                                                  uint32_t hc, uint32_t* __restrict__ err) {
+                                                  uint32_t hc, uint32_t direct_cap, uint32_t* __restrict__ err) {
   __shared__ uint32_t h[NB1];
   __shared__ uint32_t scratch[24];
   uint32_t w, b;
@@ -132,12 +127,21 @@ __global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, 
   const int64_t u = (int64_t)w * B.P + b;   // the block's arrays
   const uint32_t used = spec ? spec_used[u] : SPEC_NONE;
   const Level1 R = block_level1<1024, true>(hist1 + u * hc * NB1, hc, used, need, acc + (int64_t)w * ld_acc, B.start(b),
-                                            B.start(b + 1u), true, true, h, scratch, err);
+                                            B.start(b + 1u), h, scratch, err);
+  // the fused add's speculative candidates hold every key >= its floor, so
+  // they are usable when the floor is at or below the threshold bin
+  const bool specok = spec && R.ok && used <= (R.pfx << R.S);
+  bool direct = false;
+  if (direct_cap != 0u && specok && !R.full) {   // uniform
+    uint32_t n = 0u, cands;
+    for (uint32_t i = M_MARGIN + threadIdx.x; i < (uint32_t)NB_FLOOR; i += 1024u) n += h[i];
+    block_excl_scan(n, scratch, &cands);
+    direct = cands <= direct_cap;
+  }
   if (threadIdx.x == 0) {
     uint32_t* st = state + u * ST_WORDS;
-    // the fused add's speculative candidates hold every key >= its floor, so
-    // they are usable when the floor is at or below the threshold bin
-    st[ST_SPECOK] = (spec && R.ok && used <= (R.pfx << R.S)) ? 1u : 0u;
+    st[ST_SPECOK] = specok ? 1u : 0u;
+    st[ST_DIRECT] = direct ? 1u : 0u;
     if (spec_t1) spec_t1[u] = R.ok ? ((R.pfx << R.S) >> D1_SHIFT) + 1u : 0u;   // the next add's floor: 12-bit bins
     st[ST_T1] = R.pfx;
     st[ST_SHIFT] = R.S;
@@ -482,6 +486,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPW >= 8 ? 
   };
   if constexpr (SPW == 1) {
     const uint32_t specok = st[ST_SPECOK];
+    if (st[ST_DIRECT] != 0u) return;
     if (specok != 0u) {
       const uint32_t tlo = st[ST_T1] << st[ST_SHIFT], thi = tlo + (1u << st[ST_SHIFT]);
       const uint32_t slot = slot0 + (uint32_t)wave_id();
@@ -520,6 +525,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPW >= 8 ? 
     }
     const uint32_t specok = st[ST_SPECOK];
     const uint32_t pfx = st[ST_T1], S = st[ST_SHIFT];
+    if (st[ST_DIRECT] != 0u) return;
     if (specok != 0u) {
       const uint32_t tlo = pfx << S, thi = tlo + (1u << S);
       const int lane = lane_id();
@@ -1802,32 +1808,47 @@ __global__ __launch_bounds__(256) void k_emit(
   }
 }
 
-// ============================================================================ a3 in one workgroup per block
+// ============================================================================ a3 ended by one workgroup per block
 // A block that selects few entries (topk_one below) has its candidates in one
-// workgroup's registers: the fused add's, when they hold the whole selection
-// (at least `need` keys at or above the floor) and fit, else those the block's
-// own level-1 threshold leaves.  One launch then finds the exact threshold and
-// writes the selection, where the general path takes four dependent ones, each
-// mostly waiting; what it writes is the same.  A block the candidates do not
-// decide (its first step, a fallen threshold, entries changed since the add, or
-// more candidates than the registers hold, as a residual that piles up below
-// the threshold leaves) is first reduced to them: by k_one_prep, with workgroups enough to stream it,
-// or, up to ONE_SELF elements, by the same workgroup.  It is bound by the
-// chain of barriers and by one CU's instruction issue (a tile list's search, 7
-// to 10 LDS reads, is most of it), which is why it ends at ONE_KB entries.  The
-// four launches and this: 26 and 9 us for 16 blocks of 16384 at 1 %, 28 and
-// 22 us for 16 of 2^18 at 1 %, 33 and 20 us for 32 of 1.25M at 0.1 %, 42 and
-// 17 us for 256 of 100,000 at 1 %.
+// workgroup's registers, which finds the exact threshold and writes the
+// selection in one launch, where the general path takes k_thresh and k_emit;
+// what it writes is the same.
+//
+// ALONE: a block of up to ONE_SELF elements needs no launch before this one:
+// its candidates are the fused add's, when they hold the whole selection (at
+// least kb keys at or above the floor) and fit the registers, else those the
+// block's own level-1 threshold leaves, streamed from acc here.  Four launches
+// and this: 26 and 13 us for 16 blocks of 65536 at 1 %.
+//
+// Longer blocks come from k_select1 and k_collect, which spread a block's
+// filtering (of the add's lists however long they are, or of acc) and leave
+// the level-1 threshold.  (One workgroup that did their work took 1.7 ms where
+// they take 0.2, for blocks of 2M elements whose threshold fell by more than
+// the histogram's margin, and a 256-workgroup launch that read acc again for
+// blocks of 1M with 20000 candidates 0.26 ms where these three take 0.06.)  From
+// ONE_DIRECT slots per call k_collect leaves lists that fit the registers
+// to this kernel: a wave per slot of a few entries each costs more than this
+// one's longer list searches there (256 blocks of 1M 54 us collected and 37
+// taken as they are, 32 of 1.25M 29 and 28; but 16 of 2^18 25.8 and 26.4, 4 of
+// 2M 22.3 and 24.2).  Against k_thresh and k_emit: 29 and 26 us for 16 blocks
+// of 2^18 at 1 %, 106 and 37 us for 256 of 1M at 0.1 %, 39 and 28 us for 32 of
+// 1.25M at 0.1 %, 26 and 22 us for 4 of 2M at 0.05 %.
+//
+// Bound by the chain of barriers and by one CU's instruction issue (an entry's
+// list is found by 7 to 10 LDS reads), which is why it ends at ONE_KB entries.
+// Where ties or zeros leave more candidates than the registers hold, ALONE
+// loads them again in at most four chunks per pass, and in long blocks every
+// wave walks whole slots, in both with one LDS add for the lanes that agree on
+// a bin: 4 blocks of 2M zeros with fewer than kb other entries take 1.3 ms,
+// against 8.8 by k_thresh and k_emit and 10.6 by this kernel with a list search
+// and an LDS add per entry.
 constexpr int ONE_THREADS = 1024;
 constexpr int ONE_R = 16;                            // candidates per thread in registers
-constexpr int ONE_CAP = ONE_THREADS * ONE_R;         // a chunk; further chunks are loaded again per pass
+constexpr int ONE_CAP = ONE_THREADS * ONE_R;         // a chunk
 constexpr int ONE_LISTS = ONE_THREADS;               // most add tiles per block: a list per thread
 constexpr int ONE_KB = 4096;                         // most entries selected (staged in LDS)
 constexpr int64_t ONE_SELF = 1 << 16;
-constexpr uint32_t PREP_SLOTS = 8;                   // most slots per workgroup of k_one_prep
-// ... fewer while that makes fewer workgroups than this: 16 piled-up blocks of 2^18 took 15 us with eight slots
-// each (128 workgroups, half the CUs), 8 with two.
-constexpr int64_t PREP_GROUPS = 512;
+constexpr int64_t ONE_DIRECT = 4096;                 // slots of a call from which the add's lists are taken as they are
 
 struct TopkOne {
   const float* acc;
@@ -1835,12 +1856,11 @@ struct TopkOne {
   Blocks B;
   Units U;
   uint32_t kb, smax, add_tiles, hc;
-  int spec, self;
-  uint32_t *hist1, *state, *slot_cnt, *slot_nbin, *spec_t1, *keep, *err;
-  const uint32_t *spec_used, *spec_cnt;
+  int spec;
+  uint32_t *hist1, *state, *spec_t1, *keep, *err;
+  const uint32_t *spec_used, *spec_cnt, *slot_cnt, *slot_nbin, *bin_key;
   int32_t* cand_idx;
   float* cand_val;
-  uint32_t* bin_key;
   int32_t *out_idx, *local_idx;
   float* out_val;
 };
@@ -1851,66 +1871,15 @@ __device__ __forceinline__ uint32_t tile_candidates(const TopkOne& a, int64_t u,
   const uint32_t t0 = block_origin(s) + g * (uint32_t)ADD_TILE, t1 = t0 + (uint32_t)ADD_TILE;
   return min(a.spec_cnt[u * a.add_tiles + g], min(t1, e) - max(t0, s));
 }
-__device__ __forceinline__ uint32_t tiles_of(uint32_t s, uint32_t e) {
-  return (e - block_origin(s) + (uint32_t)ADD_TILE - 1u) / (uint32_t)ADD_TILE;
-}
-// Whether a block with this word of the add has candidates at all.
-__device__ __forceinline__ bool spec_valid(uint32_t used) { return used != SPEC_NONE && !(used & SPEC_DIRTY); }
-// Whether N candidates decide a block that selects kb.
-__device__ __forceinline__ bool spec_decides(uint32_t N, uint32_t kb) { return N >= kb && N <= (uint32_t)ONE_CAP; }
 
-// The blocks their candidates do not decide: level-1 threshold, then the
-// block's entries at or above its bin into its slots, `per` of them per
-// workgroup.  Every workgroup of a block finds the threshold itself; a block
-// that has to be counted again is left to its first one.
-__global__ __launch_bounds__(256) void k_one_prep(TopkOne a, uint32_t gq, uint32_t per) {
-  __shared__ uint32_t h[NB1];
-  __shared__ CollectSmem L;
-  __shared__ uint32_t scratch[16];
-  uint32_t w, b;
-  a.U.decode(blockIdx.x / gq, a.B.P, &w, &b);
-  const int64_t u = (int64_t)w * a.B.P + b;
-  const uint32_t s = a.B.start(b), e = a.B.start(b + 1u);
-  const uint32_t used = a.spec ? a.spec_used[u] : SPEC_NONE;
-  if (spec_valid(used)) {
-    uint32_t c = 0u, total;
-    const uint32_t nt = tiles_of(s, e);
-    for (uint32_t g = threadIdx.x; g < nt; g += 256u) c += tile_candidates(a, u, s, e, g);
-    block_excl_scan(c, scratch, &total);
-    if (spec_decides(total, a.kb)) return;   // uniform
-  }
-  const uint32_t slot0 = (blockIdx.x % gq) * per;
-  if (block_origin(s) + slot0 * (uint32_t)SLOT >= e) return;
-  const float* __restrict__ A = a.acc + (int64_t)w * a.ld_acc;
-  // counted again only by the first workgroup, which then takes the whole block
-  Level1 R = block_level1<256, false>(a.hist1 + u * a.hc * NB1, a.hc, used, a.kb, A, s, e, false, slot0 == 0u, h, scratch,
-                                     a.err);
-  uint32_t count = per;
-  if (!R.ok) {   // uniform
-    if (slot0 != 0u) return;
-    __syncthreads();
-    R = block_level1<256, false>(a.hist1 + u * a.hc * NB1, a.hc, used, a.kb, A, s, e, true, true, h, scratch, a.err);
-    count = a.smax;
-  }
-  if (slot0 == 0u && threadIdx.x == 0) {
-    uint32_t* st = a.state + u * ST_WORDS;
-    st[ST_T1] = R.pfx;
-    st[ST_SHIFT] = R.S;
-  }
-  collect_slots(A, a.B.n, w, (uint32_t)u, s, e, slot0, count, a.smax,
-                [&](uint32_t* tlo, uint32_t* S) {
-                  *S = R.S;
-                  *tlo = R.pfx << R.S;
-                },
-                L, a.slot_cnt, a.slot_nbin, a.cand_idx, a.cand_val, a.bin_key);
-}
-
+template <bool ALONE>
 __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
+  constexpr uint32_t NWV = ONE_THREADS / WAVE;
   __shared__ uint32_t h[NB1];
   __shared__ float ov[ONE_KB];
   __shared__ uint32_t pref[ONE_LISTS + 1];
-  __shared__ uint32_t cw[ONE_R * ONE_THREADS / WAVE];   // emit: per (register, wave) the counts, then those before it
-  __shared__ uint32_t scratch[24];
+  __shared__ uint32_t cw[ONE_R * NWV];   // emit: per (register, wave) the counts, then those before it
+  __shared__ uint32_t scratch[3 * NWV + 8];
   static_assert(ONE_KB <= NB1, "the selected indices are staged in the histogram's space");
   const uint32_t t = threadIdx.x;
   uint32_t w, b;
@@ -1918,65 +1887,86 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
   const int64_t u = (int64_t)w * a.B.P + b;
   const uint32_t s = a.B.start(b), e = a.B.start(b + 1u), o = block_origin(s);
   uint32_t* st = a.state + u * ST_WORDS;
-  uint32_t* __restrict__ H = a.hist1 + u * a.hc * NB1;
   int32_t* __restrict__ CI = a.cand_idx + (int64_t)w * a.B.n;
   float* __restrict__ CV = a.cand_val + (int64_t)w * a.B.n;
 
-  // ---- the candidates: nl lists, list i from max(o + i lw, s) on, of pref[i + 1] - pref[i] entries; the
-  // smallest key they may hold
-  const uint32_t used = a.spec ? a.spec_used[u] : SPEC_NONE;
-  uint32_t nl = tiles_of(s, e), lw = (uint32_t)ADD_TILE, key0 = used, N;
-  uint32_t c0 = t < nl ? tile_candidates(a, u, s, e, t) : 0u;   // (loaded with the word before)
-  const bool valid = spec_valid(used);   // uniform
-  if (!valid) c0 = 0u;
-  uint32_t ex = block_excl_scan(c0, scratch, &N);
-  const bool specok = valid && spec_decides(N, a.kb);   // uniform
-  if (!specok && a.self) {
-    const float* __restrict__ A = a.acc + (int64_t)w * a.ld_acc;
-    const Level1 R = block_level1<ONE_THREADS, false>(H, a.hc, used, a.kb, A, s, e, true, true, h, scratch, a.err);
-    key0 = R.pfx << R.S;
-    nl = 1u;
-    N = 0u;
-    for (uint32_t x0 = s; x0 < e; x0 += (uint32_t)ONE_CAP) {   // uniform
-      const uint32_t x = x0 + t * (uint32_t)ONE_R;
-      f4v v[ONE_R / 4];
+  // ---- the candidates: nl lists, list i from max(o + i lw, s) on, of pref[i + 1] - pref[i] entries
+  uint32_t nl = (e - o + (uint32_t)ADD_TILE - 1u) / (uint32_t)ADD_TILE, lw = (uint32_t)ADD_TILE, N, ex;   // the add's
+  uint32_t used = 0u, key0 = 0u;                       // ALONE: the add's word; the smallest key they may hold
+  // the level-1 threshold bin (the keys k with k >> S == pfx), its entries and how many of them are selected
+  uint32_t pfx = 0u, cnt = 0u, need = 0u;
+  int S = FINE_SHIFT;
+  bool specok = false;                                 // ALONE: the add's candidates decide
+  uint32_t cs = 0u, bs = 0u;                           // not the add's lists: thread t's slot: its entries, those in the bin
+  if constexpr (ALONE) {
+    uint32_t* __restrict__ H = a.hist1 + u * a.hc * NB1;
+    used = a.spec ? a.spec_used[u] : SPEC_NONE;
+    key0 = used;
+    uint32_t c0 = t < nl ? tile_candidates(a, u, s, e, t) : 0u;   // (loaded with the word before)
+    const bool valid = used != SPEC_NONE && !(used & SPEC_DIRTY);   // uniform: whether there are candidates
+    if (!valid) c0 = 0u;
+    ex = block_excl_scan(c0, scratch, &N);
+    specok = valid && N >= a.kb && N <= (uint32_t)ONE_CAP;   // uniform
+    if (!specok) {
+      const float* __restrict__ A = a.acc + (int64_t)w * a.ld_acc;
+      const Level1 R = block_level1<ONE_THREADS, false>(H, a.hc, used, a.kb, A, s, e, h, scratch, a.err);
+      key0 = R.pfx << R.S;
+      nl = 1u;
+      N = 0u;
+      for (uint32_t x0 = s; x0 < e; x0 += (uint32_t)ONE_CAP) {   // uniform
+        const uint32_t x = x0 + t * (uint32_t)ONE_R;
+        f4v v[ONE_R / 4];
 #pragma unroll
-      for (int q = 0; q < ONE_R / 4; ++q) {
-        const uint32_t y = x + (uint32_t)(4 * q);
-        v[q] = f4v{0.f, 0.f, 0.f, 0.f};
-        if (y < e && e - y >= 4u) {
-          v[q] = *reinterpret_cast<const f4u*>(A + y);
-        } else if (y < e) {   // the block's last elements
-          v[q].x = A[y];
-          if (y + 1u < e) v[q].y = A[y + 1u];
-          if (y + 2u < e) v[q].z = A[y + 2u];
+        for (int q = 0; q < ONE_R / 4; ++q) {
+          const uint32_t y = x + (uint32_t)(4 * q);
+          v[q] = f4v{0.f, 0.f, 0.f, 0.f};
+          if (y < e && e - y >= 4u) {
+            v[q] = *reinterpret_cast<const f4u*>(A + y);
+          } else if (y < e) {   // the block's last elements
+            v[q].x = A[y];
+            if (y + 1u < e) v[q].y = A[y + 1u];
+            if (y + 2u < e) v[q].z = A[y + 2u];
+          }
         }
-      }
-      uint32_t c = 0u, tot;
+        uint32_t c = 0u, tot;
 #pragma unroll
-      for (int r = 0; r < ONE_R; ++r) c += x + (uint32_t)r < e && mag_key(v[r / 4][r % 4]) >= key0 ? 1u : 0u;
-      uint32_t pos = N + block_excl_scan(c, scratch, &tot);
+        for (int r = 0; r < ONE_R; ++r) c += x + (uint32_t)r < e && mag_key(v[r / 4][r % 4]) >= key0 ? 1u : 0u;
+        uint32_t pos = N + block_excl_scan(c, scratch, &tot);
 #pragma unroll
-      for (int r = 0; r < ONE_R; ++r) {
-        if (x + (uint32_t)r < e && mag_key(v[r / 4][r % 4]) >= key0) {
-          CI[s + pos] = (int32_t)(x + (uint32_t)r);
-          CV[s + pos] = v[r / 4][r % 4];
-          ++pos;
+        for (int r = 0; r < ONE_R; ++r) {
+          if (x + (uint32_t)r < e && mag_key(v[r / 4][r % 4]) >= key0) {
+            CI[s + pos] = (int32_t)(x + (uint32_t)r);
+            CV[s + pos] = v[r / 4][r % 4];
+            ++pos;
+          }
         }
+        N += tot;
       }
-      N += tot;
+      ex = 0u;
     }
-    ex = 0u;
-  } else if (!specok) {
-    key0 = st[ST_T1] << st[ST_SHIFT];
-    lw = (uint32_t)SLOT;
-    nl = (e - o + lw - 1u) / lw;
-    uint32_t c = 0u;
-    if (t < nl) {
-      const uint32_t x0 = o + t * lw;
-      c = min(a.slot_cnt[u * a.smax + t], min(x0 + lw, e) - max(x0, s));
+  } else {
+    S = (int)st[ST_SHIFT];
+    pfx = st[ST_T1];
+    need = st[ST_NEED1];
+    cnt = st[ST_CNT1];
+    const uint32_t c0 = t < nl ? tile_candidates(a, u, s, e, t) : 0u;   // (loaded with the words before)
+    if (st[ST_DIRECT] != 0u) {   // uniform
+      ex = block_excl_scan(c0, scratch, &N);
+      N = min(N, (uint32_t)ONE_CAP);   // (as the level-1 select counted them)
+    } else {
+      lw = (uint32_t)SLOT;
+      nl = (e - o + lw - 1u) / lw;
+      if (t < nl) {
+        const uint32_t x0 = o + t * lw;
+        cs = min(a.slot_cnt[u * a.smax + t], min(x0 + lw, e) - max(x0, s));
+        bs = min(a.slot_nbin[u * a.smax + t], cs);
+      }
+      uint32_t x3[3] = {cs, bs, 0u}, t3[3];
+      block_excl_scan3(x3, scratch, t3);
+      ex = x3[0];
+      N = t3[0];
+      if (t == 0 && t3[1] != cnt) atomicOr(a.err, ERR_COUNT);
     }
-    ex = block_excl_scan(c, scratch, &N);
   }
   if (t < nl) pref[t] = ex;
   if (t == 0) pref[nl] = N;
@@ -2019,97 +2009,200 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
       }
     }
   };
-  if (nch > 0u) load(0u);
+  // !ALONE with more candidates than the registers hold: each wave walks whole slots
+  const bool walk = !ALONE && nch > 1u;   // uniform
+  if (nch > 0u && !walk) load(0u);
 
-  // ---- level 1: bins of 2^FINE_SHIFT keys from the smallest candidate key on, the last also holding every
-  // larger key; if the threshold falls there, bins of the top 12 key bits
-#pragma unroll
-  for (int q = 0; q < NB1 / ONE_THREADS; ++q) h[q * ONE_THREADS + (int)t] = 0u;
-  __syncthreads();
-  const uint32_t f0 = key0 >> FINE_SHIFT;
-  each([&](uint32_t key) { atomicAdd(&h[min((key >> FINE_SHIFT) - f0, (uint32_t)NB1 - 1u)], 1u); });
-  __syncthreads();
-  // the histogram copies rest at zero between steps (cleared here, behind the
-  // loads: a load issued after stores is waited for with them)
-  const uint32_t nb4 = (uint32_t)l1_map(used).bins() / 4u;   // of each copy
-  static_assert(NB1 / 4 == ONE_THREADS, "one uint4 of a copy per thread");
-  if (t < nb4)
-    for (uint32_t k = 0; k < a.hc; ++k) reinterpret_cast<uint4*>(H + k * NB1)[t] = make_uint4(0u, 0u, 0u, 0u);
-  uint32_t T, above, cnt, ok;
-  block_select_desc(h, NB1, a.kb, scratch, &T, &above, &cnt, &ok);
-  int S = FINE_SHIFT;
-  uint32_t pfx = f0 + T;
-  if (T == (uint32_t)NB1 - 1u) {   // uniform
+  // ---- ALONE: level 1 in bins of 2^FINE_SHIFT keys from the smallest candidate key on, the last also holding
+  // every larger key; if the threshold falls there, bins of the top 12 key bits
+  const bool same = nch > 1u;   // uniform: so many candidates are mostly ties
+  if constexpr (ALONE) {
+    uint32_t* __restrict__ H = a.hist1 + u * a.hc * NB1;
 #pragma unroll
     for (int q = 0; q < NB1 / ONE_THREADS; ++q) h[q * ONE_THREADS + (int)t] = 0u;
     __syncthreads();
-    each([&](uint32_t key) { atomicAdd(&h[key >> D1_SHIFT], 1u); });
+    const uint32_t f0 = key0 >> FINE_SHIFT;
+    each([&](uint32_t key) { hist_add(h, min((key >> FINE_SHIFT) - f0, (uint32_t)NB1 - 1u), same); });
     __syncthreads();
+    // the histogram copies rest at zero between steps (cleared here, behind the
+    // loads: a load issued after stores is waited for with them)
+    const uint32_t nb4 = (uint32_t)l1_map(used).bins() / 4u;   // of each copy
+    static_assert(NB1 / 4 == ONE_THREADS, "one uint4 of a copy per thread");
+    if (t < nb4)
+      for (uint32_t k = 0; k < a.hc; ++k) reinterpret_cast<uint4*>(H + k * NB1)[t] = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t T, above, ok;
     block_select_desc(h, NB1, a.kb, scratch, &T, &above, &cnt, &ok);
-    S = D1_SHIFT;
-    pfx = T;
+    pfx = f0 + T;
+    if (T == (uint32_t)NB1 - 1u) {   // uniform
+#pragma unroll
+      for (int q = 0; q < NB1 / ONE_THREADS; ++q) h[q * ONE_THREADS + (int)t] = 0u;
+      __syncthreads();
+      each([&](uint32_t key) { hist_add(h, key >> D1_SHIFT, same); });
+      __syncthreads();
+      block_select_desc(h, NB1, a.kb, scratch, &T, &above, &cnt, &ok);
+      S = D1_SHIFT;
+      pfx = T;
+    }
+    if (!ok && t == 0) atomicOr(a.err, ERR_COUNT);
+    need = ok ? a.kb - above : 0u;
+    if (!ok) cnt = 0u;
+    if (t == 0 && a.spec_t1) a.spec_t1[u] = ok ? ((pfx << S) >> D1_SHIFT) + 1u : 0u;   // the next add's floor: 12-bit bins
   }
-  if (!ok && t == 0) atomicOr(a.err, ERR_COUNT);
+  // thread t's slot in LDS: its entries and those in the bin, later the counts before it
+  __shared__ uint32_t sc[ALONE ? 1 : ONE_LISTS], sb[ALONE ? 1 : ONE_LISTS], sg[ALONE ? 1 : ONE_LISTS],
+      se[ALONE ? 1 : ONE_LISTS];
+  const int lane = lane_id(), wv = wave_id();
+  // f(key, live) for the threshold-bin keys of slot i, a wave's 64 at a time
+  auto slot_bin = [&](uint32_t i, auto f) {
+    const uint32_t* __restrict__ K = a.bin_key + (int64_t)w * a.B.n + max(o + i * lw, s);
+    const uint32_t c = sb[i];
+    constexpr int R = 8;
+    for (uint32_t p0 = 0; p0 < c; p0 += WAVE * R) {
+      uint32_t k[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint32_t p = p0 + (uint32_t)(r * WAVE + lane);
+        k[r] = p < c ? K[p] : 0u;
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) f(k[r], p0 + (uint32_t)(r * WAVE + lane) < c);
+    }
+  };
+  if (walk) {
+    if (t < nl) {
+      sc[t] = cs;
+      sb[t] = bs;
+    }
+    __syncthreads();
+  }
   uint32_t tge, teq, need_eq;
-  resolve_bin(pfx, S, ok ? a.kb - above : 0u, ok ? cnt : 0u, h, scratch, a.err,
+  resolve_bin(pfx, S, need, cnt, h, scratch, a.err,
               [&](auto f) {
-                each([&](uint32_t key) {
-                  if ((key >> S) == pfx) f(key);
-                });
+                if (walk) {
+                  for (uint32_t i = (uint32_t)wv; i < nl; i += NWV)
+                    slot_bin(i, [&](uint32_t key, bool live) {
+                      if (live && (key >> S) == pfx) f(key);
+                    });
+                } else {
+                  each([&](uint32_t key) {
+                    if ((key >> S) == pfx) f(key);
+                  });
+                }
               },
-              tge, teq, need_eq);
+              tge, teq, need_eq, same);
 
   // ---- emit in index order: an entry's place is the entries >= TGE before it plus the ties taken before
   // it; staged in LDS, then written as whole lines
-  const int lane = lane_id(), wv = wave_id();
   const uint64_t lt = __lanemask_lt();
-  constexpr uint32_t NWV = ONE_THREADS / WAVE;
   int32_t* oi = reinterpret_cast<int32_t*>(h);
   uint32_t run_g = 0u, run_e = 0u;
   __syncthreads();   // the histogram's space is read no more
-  for (uint32_t c = 0; c < nch; ++c) {
-    if (nch > 1u) load(c);   // uniform
-#pragma unroll
-    for (int r = 0; r < ONE_R; ++r) {
-      if ((uint32_t)r < per) {   // uniform
-        const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
-        const uint32_t key = mag_key(vx[r]);
-        const uint32_t g = popc64(__ballot(live && key >= tge));
-        const uint32_t q = popc64(__ballot(live && need_eq != 0u && key == teq));
-        if (lane == 0) cw[(uint32_t)r * NWV + (uint32_t)wv] = g | (q << 16);
+  // a wave's 64 entries, gp entries >= TGE and ep ties before them
+  auto put = [&](int32_t i, float v, uint64_t mg, uint64_t me, bool is_ge, bool is_eq, uint32_t gp, uint32_t ep) {
+    gp += popc64(mg & lt);
+    ep += popc64(me & lt);
+    if (a.keep && is_eq && ep + 1u == need_eq) a.keep[u * KEEP_WORDS + KEEP_CUT] = (uint32_t)i;   // the last tie taken
+    if (is_ge || (is_eq && ep < need_eq)) {
+      const uint32_t pos = gp + min(ep, need_eq);
+      if (pos < a.kb) {
+        oi[pos] = i;
+        ov[pos] = v;
+      } else {
+        atomicOr(a.err, ERR_COUNT_POS);
+      }
+    }
+  };
+  if (walk) {
+    // per slot the entries selected by key and the ties: those above the bin, and the bin's
+    for (uint32_t i = (uint32_t)wv; i < nl; i += NWV) {
+      uint32_t g = sc[i] - sb[i], q = 0u;
+      slot_bin(i, [&](uint32_t key, bool live) {
+        g += popc64(__ballot(live && key >= tge));
+        q += popc64(__ballot(live && need_eq != 0u && key == teq));
+      });
+      if (lane == 0) {
+        sg[i] = g;
+        se[i] = q;
       }
     }
     __syncthreads();
-    static_assert(ONE_CAP < (1 << 16), "packed counts of a chunk");
-    uint32_t tot;
-    const uint32_t mine = t < per * NWV ? cw[t] : 0u;
-    const uint32_t before = block_excl_scan(mine, scratch, &tot);
-    if (t < per * NWV) cw[t] = before;
+    const uint32_t g = t < nl ? sg[t] : 0u, q = t < nl ? se[t] : 0u;
+    uint32_t x3[3] = {g, q, 0u}, t3[3];
+    block_excl_scan3(x3, scratch, t3);
+    run_g = t3[0];
+    run_e = t3[1];
+    if (t < nl) {
+      sg[t] = x3[0];
+      se[t] = x3[1];
+      if (g == 0u && (q == 0u || x3[1] >= need_eq)) sc[t] = 0u;   // nothing of the slot is selected
+    }
     __syncthreads();
+    for (uint32_t i = (uint32_t)wv; i < nl; i += NWV) {
+      const uint32_t c = sc[i];
+      const int64_t at = max(o + i * lw, s);
+      uint32_t gp = sg[i], ep = se[i];
+      constexpr int R = 8;
+      for (uint32_t p0 = 0; p0 < c; p0 += WAVE * R) {
+        int32_t i1[R];
+        float v1[R];
 #pragma unroll
-    for (int r = 0; r < ONE_R; ++r) {
-      if ((uint32_t)r < per) {   // uniform
-        const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
-        const uint32_t key = mag_key(vx[r]);
-        const bool is_ge = live && key >= tge, is_eq = live && need_eq != 0u && key == teq;
-        const uint64_t mg = __ballot(is_ge), me = __ballot(is_eq);
-        const uint32_t x = cw[(uint32_t)r * NWV + (uint32_t)wv];
-        const uint32_t gp = run_g + (x & 0xFFFFu) + popc64(mg & lt), ep = run_e + (x >> 16) + popc64(me & lt);
-        if (a.keep && is_eq && ep + 1u == need_eq) a.keep[u * KEEP_WORDS + KEEP_CUT] = (uint32_t)ix[r];   // the last tie taken
-        if (is_ge || (is_eq && ep < need_eq)) {
-          const uint32_t pos = gp + min(ep, need_eq);
-          if (pos < a.kb) {
-            oi[pos] = ix[r];
-            ov[pos] = vx[r];
-          } else {
-            atomicOr(a.err, ERR_COUNT_POS);
+        for (int r = 0; r < R; ++r) {
+          const uint32_t p = p0 + (uint32_t)(r * WAVE + lane);
+          i1[r] = 0;
+          v1[r] = 0.f;
+          if (p < c) {
+            i1[r] = CI[at + p];
+            v1[r] = CV[at + p];
           }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const bool live = p0 + (uint32_t)(r * WAVE + lane) < c;
+          const uint32_t key = mag_key(v1[r]);
+          const bool is_ge = live && key >= tge, is_eq = live && need_eq != 0u && key == teq;
+          const uint64_t mg = __ballot(is_ge), me = __ballot(is_eq);
+          put(i1[r], v1[r], mg, me, is_ge, is_eq, gp, ep);
+          gp += popc64(mg);
+          ep += popc64(me);
         }
       }
     }
-    run_g += tot & 0xFFFFu;
-    run_e += tot >> 16;
-    __syncthreads();   // cw is written again
+    __syncthreads();   // the staged selection is complete
+  } else {
+    for (uint32_t c = 0; c < nch; ++c) {
+      if (nch > 1u) load(c);   // uniform
+#pragma unroll
+      for (int r = 0; r < ONE_R; ++r) {
+        if ((uint32_t)r < per) {   // uniform
+          const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
+          const uint32_t key = mag_key(vx[r]);
+          const uint32_t g = popc64(__ballot(live && key >= tge));
+          const uint32_t q = popc64(__ballot(live && need_eq != 0u && key == teq));
+          if (lane == 0) cw[(uint32_t)r * NWV + (uint32_t)wv] = g | (q << 16);
+        }
+      }
+      __syncthreads();
+      static_assert(ONE_CAP < (1 << 16), "packed counts of a chunk");
+      uint32_t tot;
+      const uint32_t mine = t < per * NWV ? cw[t] : 0u;
+      const uint32_t before = block_excl_scan(mine, scratch, &tot);
+      if (t < per * NWV) cw[t] = before;
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < ONE_R; ++r) {
+        if ((uint32_t)r < per) {   // uniform
+          const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
+          const uint32_t key = mag_key(vx[r]);
+          const bool is_ge = live && key >= tge, is_eq = live && need_eq != 0u && key == teq;
+          const uint64_t mg = __ballot(is_ge), me = __ballot(is_eq);
+          const uint32_t x = cw[(uint32_t)r * NWV + (uint32_t)wv];
+          put(ix[r], vx[r], mg, me, is_ge, is_eq, run_g + (x & 0xFFFFu), run_e + (x >> 16));
+        }
+      }
+      run_g += tot & 0xFFFFu;
+      run_e += tot >> 16;
+      __syncthreads();   // cw is written again
+    }
   }
   const uint32_t taken = run_g + min(run_e, need_eq);
   const int64_t out = u * a.kb;
@@ -2120,8 +2213,7 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
   }
   if (t == 0) {
     if (taken != a.kb) atomicOr(a.err, ERR_COUNT_SUM);
-    st[ST_SPECOK] = specok ? 1u : 0u;
-    if (a.spec_t1) a.spec_t1[u] = ok ? ((pfx << S) >> D1_SHIFT) + 1u : 0u;   // the next add's floor: 12-bit bins
+    if constexpr (ALONE) st[ST_SPECOK] = specok ? 1u : 0u;
     if (a.keep) {
       uint32_t* kp = a.keep + u * KEEP_WORDS;
       kp[KEEP_TGE] = tge;
@@ -2134,9 +2226,10 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
 // ============================================================================ launchers
 hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
                            int32_t kb, int32_t smax, int32_t add_tiles, bool spec, uint32_t* hist1, uint32_t* state,
-                           uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt, uint32_t* slot_cnt,
-                           uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val, uint32_t* bin_key, int32_t* out_idx,
-                           float* out_val, int32_t* local_idx, uint32_t* keep, uint32_t* err, hipStream_t s) {
+                           uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt,
+                           const uint32_t* slot_cnt, const uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val,
+                           const uint32_t* bin_key, int32_t* out_idx, float* out_val, int32_t* local_idx,
+                           uint32_t* keep, uint32_t* err, hipStream_t s) {
   TopkOne a;
   a.acc = acc;
   a.ld_acc = ld_acc;
@@ -2147,38 +2240,35 @@ hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, con
   a.add_tiles = (uint32_t)add_tiles;
   a.hc = hist_copies_for(n, P);
   a.spec = spec ? 1 : 0;
-  a.self = (n + P - 1) / P <= ONE_SELF ? 1 : 0;
   a.hist1 = hist1;
   a.state = state;
-  a.slot_cnt = slot_cnt;
-  a.slot_nbin = slot_nbin;
   a.spec_t1 = spec_t1;
   a.keep = keep;
   a.err = err;
   a.spec_used = spec_used;
   a.spec_cnt = spec_cnt;
+  a.slot_cnt = slot_cnt;
+  a.slot_nbin = slot_nbin;
+  a.bin_key = bin_key;
   a.cand_idx = cand_idx;
   a.cand_val = cand_val;
-  a.bin_key = bin_key;
   a.out_idx = out_idx;
   a.local_idx = local_idx;
   a.out_val = out_val;
-  if (!a.self) {
-    const uint32_t per = (uint32_t)std::clamp<int64_t>(nunits * smax / PREP_GROUPS, 1, PREP_SLOTS);
-    const uint32_t gq = ((uint32_t)smax + per - 1u) / per;
-    hipLaunchKernelGGL(k_one_prep, dim3((unsigned)(nunits * gq)), dim3(256), 0, s, a, gq, per);
-  }
-  hipLaunchKernelGGL(k_topk_one, dim3((unsigned)nunits), dim3(ONE_THREADS), 0, s, a);
+  if (topk_alone(n, P)) hipLaunchKernelGGL(k_topk_one<true>, dim3((unsigned)nunits), dim3(ONE_THREADS), 0, s, a);
+  else hipLaunchKernelGGL(k_topk_one<false>, dim3((unsigned)nunits), dim3(ONE_THREADS), 0, s, a);
   return hipGetLastError();
 }
 
 bool topk_one(int32_t kb, int64_t add_tiles) { return kb <= ONE_KB && add_tiles <= ONE_LISTS; }
+bool topk_alone(int64_t n, int32_t P) { return (n + P - 1) / P <= ONE_SELF; }
 
 hipError_t launch_select1(uint32_t* hist1, uint32_t* state, int64_t nunits, const Units& U, int64_t n, int32_t P,
                           uint32_t need, uint32_t* spec_t1, const uint32_t* spec_used, bool spec, const float* acc,
-                          int64_t ld_acc, uint32_t* err, hipStream_t s) {
+                          int64_t ld_acc, int32_t smax, bool one, uint32_t* err, hipStream_t s) {
   hipLaunchKernelGGL(k_select1, dim3((unsigned)nunits), dim3(1024), 0, s, hist1, state, make_blocks(n, P), U, need,
-                     spec_t1, spec_used, spec ? 1 : 0, acc, ld_acc, hist_copies_for(n, P), err);
+                     spec_t1, spec_used, spec ? 1 : 0, acc, ld_acc, hist_copies_for(n, P),
+                     one && nunits * smax >= ONE_DIRECT ? (uint32_t)ONE_CAP : 0u, err);
   return hipGetLastError();
 }
 

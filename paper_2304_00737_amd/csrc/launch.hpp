@@ -58,15 +58,18 @@ hipError_t launch_hist1(const float* acc, int64_t ld_acc, int64_t nunits, const 
                         uint32_t* hist1, hipStream_t s);
 hipError_t launch_select1(uint32_t* hist1, uint32_t* state, int64_t nunits, const Units& U, int64_t n, int32_t P,
                           uint32_t need, uint32_t* spec_t1, const uint32_t* spec_used, bool spec, const float* acc,
-                          int64_t ld_acc, uint32_t* err, hipStream_t s);
-// The whole block top-k after the level-1 histograms in one workgroup per
-// unit, for blocks topk_one takes.
+                          int64_t ld_acc, int32_t smax, bool one, uint32_t* err, hipStream_t s);
+// The end of the block top-k (exact threshold and emit) in one workgroup per
+// unit, for blocks topk_one takes; for those topk_alone takes all of it after
+// the level-1 histograms.
 bool topk_one(int32_t kb, int64_t add_tiles);
+bool topk_alone(int64_t n, int32_t P);
 hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
                            int32_t kb, int32_t smax, int32_t add_tiles, bool spec, uint32_t* hist1, uint32_t* state,
-                           uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt, uint32_t* slot_cnt,
-                           uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val, uint32_t* bin_key, int32_t* out_idx,
-                           float* out_val, int32_t* local_idx, uint32_t* keep, uint32_t* err, hipStream_t s);
+                           uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt,
+                           const uint32_t* slot_cnt, const uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val,
+                           const uint32_t* bin_key, int32_t* out_idx, float* out_val, int32_t* local_idx,
+                           uint32_t* keep, uint32_t* err, hipStream_t s);
 hipError_t launch_collect(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
                           int32_t kb, int32_t smax, const uint32_t* state, const uint32_t* spec_cnt,
                           int32_t add_tiles, uint32_t* slot_cnt, uint32_t* slot_nbin, int32_t* cand_idx,
