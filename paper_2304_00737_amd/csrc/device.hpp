@@ -46,17 +46,25 @@ __device__ __forceinline__ uint32_t hist_floor(uint32_t F) {
 // floor the histogram counts only keys at or above FH = hist_floor(F), two
 // binades lower: the keys in [FH, F) in bins of the top 12 key bits (bins 0
 // .. M_MARGIN - 1), the keys from F up -- the speculative candidates, a few
-// per cent of the block -- in bins of 2^FINE_SHIFT keys (1/256 binade, bins
-// M_MARGIN .. NB_FLOOR - 1, the last also holding every larger key), so that
-// a threshold bin among the candidates holds few entries while a tile still
-// touches few bins, and every tile clears and flushes, and the select sums,
-// NB_FLOOR of them (7.9 binades above F: a threshold that rises further in one
-// step has its block counted again).  Bin order is key order throughout.  Without a floor (a
-// block's first step, or a histogram made without the add) every key counts
-// and a bin is the top 12 key bits.  The fused add, the lazy receipts that
-// keep its histograms exact and the level-1 select all bin through this map.
+// per cent of the block -- in N_FINE bins of 2^FINE_SHIFT keys (1/256 binade,
+// 7.3 binades), so that a threshold bin among the candidates holds few entries
+// while a tile still touches few bins, and the keys above those, where a
+// threshold lies that rose by a factor of 160 in one step, in bins of the top
+// 12 key bits again (9 binades; the last also holds every larger key).  Every
+// tile clears and flushes, and the select sums, NB_FLOOR bins: fine ones alone
+// would end 7.9 binades above F, and a threshold beyond has its block counted
+// again by one workgroup (a rise by 1000 for 64 blocks of 3.2M: 717 us of top-k
+// then, 450 this way, 442 with 4096 fine bins).  Bin order is key order
+// throughout.  Without a floor (a block's first step, or a histogram made
+// without the add) every key counts and a bin is the top 12 key bits.  The
+// fused add, the lazy receipts that keep its histograms exact and the level-1
+// select all bin through this map.
 constexpr uint32_t M_MARGIN = HIST_MARGIN;   // 12-bit bins below the candidate floor
 constexpr int NB_FLOOR = NB1 / 2;            // bins of a histogram with a floor
+constexpr uint32_t N_COARSE = 144;           // 12-bit bins above the fine ones
+constexpr uint32_t N_FINE = (uint32_t)NB_FLOOR - M_MARGIN - N_COARSE;
+constexpr int FINE_PER_D1 = D1_SHIFT - FINE_SHIFT;   // log2 of the fine bins in a 12-bit one
+static_assert(N_FINE % (1u << FINE_PER_D1) == 0u, "the fine bins end with a 12-bit one (F starts one)");
 struct L1Map {
   uint32_t floor;   // smallest key counted (FH)
   uint32_t cand;    // the candidate floor F (fine bins from here)
@@ -64,10 +72,12 @@ struct L1Map {
   __device__ __forceinline__ uint32_t bin(uint32_t key) const {
     if (!fine) return key >> D1_SHIFT;
     if (key < cand) return (key >> D1_SHIFT) - (floor >> D1_SHIFT);   // key >= floor
-    return M_MARGIN + min((key >> FINE_SHIFT) - (cand >> FINE_SHIFT), (uint32_t)NB_FLOOR - 1u - M_MARGIN);
+    const uint32_t f = (key >> FINE_SHIFT) - (cand >> FINE_SHIFT);
+    // (below N_FINE the difference wraps, so the larger of the two limits stands)
+    return M_MARGIN + min(f, N_FINE + min((f >> FINE_PER_D1) - (N_FINE >> FINE_PER_D1), N_COARSE - 1u));
   }
-  // the keys of bin T: k >> *S == *pfx; false for the last fine bin, which
-  // also holds every larger key
+  // the keys of bin T: k >> *S == *pfx; false for the last bin, which also
+  // holds every larger key
   __device__ __forceinline__ bool bin_keys(uint32_t T, uint32_t* pfx, uint32_t* S) const {
     if (!fine) {
       *pfx = T;
@@ -79,8 +89,13 @@ struct L1Map {
       *S = D1_SHIFT;
       return true;
     }
-    *pfx = (cand >> FINE_SHIFT) + (T - M_MARGIN);
-    *S = FINE_SHIFT;
+    if (T < M_MARGIN + N_FINE) {
+      *pfx = (cand >> FINE_SHIFT) + (T - M_MARGIN);
+      *S = FINE_SHIFT;
+      return true;
+    }
+    *pfx = (cand >> D1_SHIFT) + (T - M_MARGIN - N_FINE) + (N_FINE >> FINE_PER_D1);
+    *S = D1_SHIFT;
     return T != (uint32_t)NB_FLOOR - 1u;
   }
   __device__ __forceinline__ int bins() const { return fine ? NB_FLOOR : NB1; }
@@ -92,7 +107,7 @@ __device__ __forceinline__ L1Map l1_map(uint32_t used) {
   m.floor = hist_floor(used);
   return m;
 }
-static_assert(HIST_MARGIN < (uint32_t)NB_FLOOR / 2, "the 12-bit margin bins leave most bins fine");
+static_assert(M_MARGIN + N_COARSE < (uint32_t)NB_FLOOR / 2, "most bins are fine");
 
 // Adds one to word i of an LDS histogram.  `same` (uniform): the lanes mostly
 // agree on i; those that agree with the first one then add once for all of
