@@ -72,7 +72,7 @@ enum : int {
   ST_NEED2 = 10,    // ... entries still needed from that level-2 bin
   ST_STAGE = 11,    // ... 2 while level 3 is still needed, else 0
   ST_WBASE = 12,    // merge: first fine key bin (key >> FINE_SHIFT) of the union's level-1 histogram window
-  ST_DIRECT = 13,   // block top-k ended by one workgroup: it takes the fused add's lists as they are
+  ST_DIRECT = 13,   // block top-k ended by one workgroup: entries of the fused add's lists if it takes them as they are, else 0
   ST_SHIFT = 14,    // block top-k and staged threshold: the level-1 bin is the keys k with k >> ST_SHIFT == ST_T1
   ST_WORDS = 16
 };

@@ -131,17 +131,17 @@ __global__ __launch_bounds__(1024) void k_select1(uint32_t* __restrict__ hist1, 
   // the fused add's speculative candidates hold every key >= its floor, so
   // they are usable when the floor is at or below the threshold bin
   const bool specok = spec && R.ok && used <= (R.pfx << R.S);
-  bool direct = false;
+  uint32_t direct = 0u;   // the candidates (at least need) if they are few enough
   if (direct_cap != 0u && specok && !R.full) {   // uniform
     uint32_t n = 0u, cands;
     for (uint32_t i = M_MARGIN + threadIdx.x; i < (uint32_t)NB_FLOOR; i += 1024u) n += h[i];
     block_excl_scan(n, scratch, &cands);
-    direct = cands <= direct_cap;
+    direct = cands <= direct_cap ? cands : 0u;
   }
   if (threadIdx.x == 0) {
     uint32_t* st = state + u * ST_WORDS;
     st[ST_SPECOK] = specok ? 1u : 0u;
-    st[ST_DIRECT] = direct ? 1u : 0u;
+    st[ST_DIRECT] = direct;
     if (spec_t1) spec_t1[u] = R.ok ? ((R.pfx << R.S) >> D1_SHIFT) + 1u : 0u;   // the next add's floor: 12-bit bins
     st[ST_T1] = R.pfx;
     st[ST_SHIFT] = R.S;
@@ -1880,6 +1880,7 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
   __shared__ uint32_t pref[ONE_LISTS + 1];
   __shared__ uint32_t cw[ONE_R * NWV];   // emit: per (register, wave) the counts, then those before it
   __shared__ uint32_t scratch[3 * NWV + 8];
+  __shared__ uint32_t counted[NWV];      // ALONE: the add's histogram's candidates, by wave
   static_assert(ONE_KB <= NB1, "the selected indices are staged in the histogram's space");
   const uint32_t t = threadIdx.x;
   uint32_t w, b;
@@ -1950,9 +1951,11 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
     need = st[ST_NEED1];
     cnt = st[ST_CNT1];
     const uint32_t c0 = t < nl ? tile_candidates(a, u, s, e, t) : 0u;   // (loaded with the words before)
-    if (st[ST_DIRECT] != 0u) {   // uniform
+    const uint32_t direct = st[ST_DIRECT];
+    if (direct != 0u) {   // uniform
       ex = block_excl_scan(c0, scratch, &N);
-      N = min(N, (uint32_t)ONE_CAP);   // (as the level-1 select counted them)
+      if (t == 0 && N != direct) atomicOr(a.err, ERR_COUNT);
+      N = min(N, (uint32_t)ONE_CAP);
     } else {
       lw = (uint32_t)SLOT;
       nl = (e - o + lw - 1u) / lw;
@@ -2022,12 +2025,30 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
     for (int q = 0; q < NB1 / ONE_THREADS; ++q) h[q * ONE_THREADS + (int)t] = 0u;
     __syncthreads();
     const uint32_t f0 = key0 >> FINE_SHIFT;
+    // the add's histogram, which the level-1 threshold below is not taken from,
+    // has to hold the same candidates
+    const uint32_t nb4 = (uint32_t)l1_map(used).bins() / 4u;   // of each copy
+    static_assert(NB1 / 4 == ONE_THREADS && M_MARGIN % 4 == 0, "one uint4 of a copy per thread");
+    static_assert(ONE_SELF <= 512ll * HCOPIES_MIN * ADD_TILE, "these blocks have HCOPIES_MIN copies");
+    uint4 c4[HCOPIES_MIN];
+    const bool sums = specok && t >= M_MARGIN / 4u && t < nb4;
+    if (sums) {
+#pragma unroll
+      for (uint32_t k = 0; k < HCOPIES_MIN; ++k) c4[k] = reinterpret_cast<const uint4*>(H + k * NB1)[t];
+    }
     each([&](uint32_t key) { hist_add(h, min((key >> FINE_SHIFT) - f0, (uint32_t)NB1 - 1u), same); });
+    if (specok) {   // uniform
+      uint32_t n = 0u;
+      if (sums) {
+#pragma unroll
+        for (uint32_t k = 0; k < HCOPIES_MIN; ++k) n += c4[k].x + c4[k].y + c4[k].z + c4[k].w;
+      }
+      n = wave_incl_scan(n);
+      if (lane_id() == WAVE - 1) counted[wave_id()] = n;
+    }
     __syncthreads();
     // the histogram copies rest at zero between steps (cleared here, behind the
     // loads: a load issued after stores is waited for with them)
-    const uint32_t nb4 = (uint32_t)l1_map(used).bins() / 4u;   // of each copy
-    static_assert(NB1 / 4 == ONE_THREADS, "one uint4 of a copy per thread");
     if (t < nb4)
       for (uint32_t k = 0; k < a.hc; ++k) reinterpret_cast<uint4*>(H + k * NB1)[t] = make_uint4(0u, 0u, 0u, 0u);
     uint32_t T, above, ok;
@@ -2213,7 +2234,14 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
   }
   if (t == 0) {
     if (taken != a.kb) atomicOr(a.err, ERR_COUNT_SUM);
-    if constexpr (ALONE) st[ST_SPECOK] = specok ? 1u : 0u;
+    if constexpr (ALONE) {
+      st[ST_SPECOK] = specok ? 1u : 0u;
+      if (specok) {
+        uint32_t n = 0u;
+        for (uint32_t i = 0; i < NWV; ++i) n += counted[i];
+        if (n != N) atomicOr(a.err, ERR_COUNT);
+      }
+    }
     if (a.keep) {
       uint32_t* kp = a.keep + u * KEEP_WORDS;
       kp[KEEP_TGE] = tge;

@@ -138,3 +138,32 @@ def test_topk_one_takes_the_adds_candidates(P, n, kb, cands):
             want_i, want_v = so.local_sparsify(g[w, bounds[b]:bounds[b + 1]], bounds[b], kb)
             assert_idx_equal(sp_idx[w, b].cpu().numpy(), want_i, f"indices w={w} b={b}")
             assert_bits_equal(sp_val[w, b].cpu().numpy(), want_v, f"values w={w} b={b}")
+
+
+# blocks the workgroup has alone, blocks filtered before it, blocks whose lists it takes as they are, the general path
+@pytest.mark.parametrize("P,n,kb", [(4, 4 * 4096, 41), (2, 2 * 65_536, 300), (2, 1 << 19, 700), (16, 16 * 65_600, 30),
+                                    (2, 200_000, 5000)])
+@pytest.mark.parametrize("before", [0, 1, 2])
+def test_two_adds_before_a_topk(P, n, kb, before):
+    """A second add before the block top-k leaves histograms of twice the
+    entries: the error word says so, in a block's first step and in later ones,
+    and a prepared workspace works again."""
+    log(f"two adds before a top-k P={P} n={n} kb={kb} after {before} steps")
+    ws = spardl.workspace(P, P, n, kb)
+    acc = torch.zeros((P, n), device="cuda")
+    sp_idx = torch.empty((P, P, kb), dtype=torch.int32, device="cuda")
+    sp_val, local = torch.empty((P, P, kb), device="cuda"), torch.empty_like(sp_idx)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+
+    def step(adds):
+        for _ in range(adds):
+            spardl.residual_add(acc, torch.empty_like(acc).normal_(generator=gen), P, n, P, ws, kb)
+        spardl.block_topk(acc, P, n, P, kb, sp_idx, sp_val, local, ws, spardl.TOPK_HIST_READY)
+        return spardl.ws_error(ws)
+
+    for _ in range(before):
+        assert step(1) == 0
+    assert step(2) & 2, "the histograms hold more than the blocks"
+    spardl.workspace_init(ws, P, P, n, kb)
+    for _ in range(2):
+        assert step(1) == 0
