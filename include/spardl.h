@@ -173,8 +173,7 @@ int spardl_residual_add_collect(float* acc, int64_t ld_acc, const float* grad, i
  * drop_cnt too) and adds only entries inside its tile, so a range a tile
  * kept from an earlier step adds nothing.  drop_idx / drop_cnt: HOST
  * arrays of l DEVICE pointers, as for spardl_residual_collect.  Nothing is
- * enqueued where the add collects without an index (P = 1, P > 65536, or large
- * sparse steps, which the separate kernels collect).
+ * enqueued for P = 1 and P > 65536, where the add collects without an index.
  * The index lives in the part of the workspace that does not grow with its
  * rows, so any workspace for these sizes holds it (a workspace for fewer
  * rows than P included).

@@ -562,7 +562,8 @@ int spardl_residual_collect_index(int32_t w0, int32_t nworkers, int64_t n, int32
   const size_t need = spardl_workspace_bytes(1, P, n, k_blk);
   if (need == 0) return SPARDL_EINVAL;
   if (ws_bytes < need) return SPARDL_ECAPACITY;
-  if (l == 0 || !collect_in_add(P, n, k_blk, l)) return SPARDL_OK;   // the add collects without an index
+  // the index is built, and the lists with it checked, also where the add will collect by the separate kernels
+  if (l == 0 || l > COLLECT_MAX_STEPS) return SPARDL_OK;
   const Layout L = make_layout(P, n, k_blk);
   Ws w = carve(ws, ws_bytes, L);
   std::vector<const float*> no_val(l, nullptr);

@@ -91,3 +91,20 @@ def test_collection_in_the_add_or_before_it(n, kb, rows):
     deferred.flush()
     check_ws(deferred)
     assert torch.equal(deferred.acc.view(torch.int32), own.acc.view(torch.int32)), "residual"
+
+
+# the collection in the add's tiles; before the add, even and ragged rows
+@pytest.mark.parametrize("n,kb", [(4096, 40), (2 ** 26, 1000), (2 ** 26 + 3, 1000)])
+def test_unsorted_drops_are_reported(n, kb):
+    """A drop list that is not sorted inside its block sets the error word when
+    its index is built, wherever the collection will run."""
+    P = 2
+    log(f"unsorted drops n={n} kb={kb}")
+    st = spardl.SparDLStep(P, n, kb, fuse_collect=True)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    st.step(torch.empty((P, n), device="cuda").normal_(generator=gen))
+    check_ws(st)
+    assert int(st.drop_cnt[0][0, 0]) >= 2
+    st.drop_idx[0][0, 0, :2] = st.drop_idx[0][0, 0, :2].flip(0)
+    spardl.residual_collect_index(0, P, n, P, kb, st.drop_idx, st.drop_cnt, st.ws)
+    assert spardl.ws_error(st.ws) & 64, "ERR_DROPS"
