@@ -150,9 +150,9 @@ int spardl_residual_add(float* acc, int64_t ld_acc, const float* grad, int64_t l
  * them and as for spardl_residual_collect (the decode's bitmap; HOST arrays
  * of l DEVICE pointers, element i-1 the buffers of SRS step i for all P
  * workers; they may be NULL when P = 1).  acc, grad, local_idx: the rows
- * w0 .. w0 + nworkers - 1 (local_idx as spardl_block_topk wrote it: large
- * sparse steps, and P > 65536, are collected by the separate kernels before
- * the add, which read it).  The drops are read through a per-tile
+ * w0 .. w0 + nworkers - 1 (local_idx is not read: large sparse steps, which
+ * separate kernels collect before the add, take the selected indices from ws,
+ * where that spardl_block_topk kept them).  The drops are read through a per-tile
  * index that spardl_residual_collect_index must have built in ws after the
  * previous step's SRS steps, for these rows and these drop lists.
  * Errors: as for spardl_residual_add with ws, plus EINVAL for NULL

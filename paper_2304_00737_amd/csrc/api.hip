@@ -40,18 +40,36 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // candidate value, threshold-bin key).
 struct Layout {
   size_t err = 0, bitmap = 0, hist1 = 0, spec_t1 = 0, spec_used = 0, spec_cnt = 0, state = 0, slot_cnt = 0,
-         slot_nbin = 0, pre_all = 0, pre_ge = 0, pre_eq = 0, keep = 0, dtile = 0;
+         slot_nbin = 0, pre_all = 0, pre_ge = 0, pre_eq = 0, keep = 0, dtile = 0, sel = 0;
   int64_t dtile_pairs = 0;   // (pair, step) lists of all rows over the SRS steps
+  bool has_sel = false;      // the collection may run in kernels before the next add
   uint32_t hcopies = HCOPIES_MIN;   // level-1 histogram copies per unit
   size_t fixed_end = 0;
   int64_t units = 0, tiles_tk = 0, tiles_mg = 0, slot_n = 0, pairs_max = 0, add_tiles = 0;
 };
 
+// Whether the add that follows a step applies that step's residual collection
+// to its tiles (k_residual_add4 with COLL); otherwise the collection's own
+// kernels run before the plain add, with the same results.  In the tiles it
+// costs time per element streamed, on its own time per entry selected or
+// dropped, scattered, and a launch per SRS step, so it goes into the add for
+// small steps and dense ones.  Whole steps, in the add and apart: P = 8, n =
+// 25.6M at 1 % 619 and 617 us; n = 138M at 0.5 % 2822 and 2672; P = 16, n =
+// 110M at 1 % 4489 and 4394; P = 14, n = 20,033,001 at 1 % 856 and 822; P =
+// 4, n = 50M at 0.1 % 584 and 566, at 1.5 % 677 and 677; but P = 8, n = 8.4M
+// at 1 % 282 and 288, at 0.3 % 243 and 251; P = 6, n = 15M at 10 % 571 and
+// 603.
+bool collect_in_add(int32_t P, int64_t n, int32_t kb, int32_t l) {
+  if (l > COLLECT_MAX_STEPS) return false;   // more SRS steps than the add takes
+  return (int64_t)P * n < (1ll << 27) || 64ll * kb * P > n;
+}
+
 // rows: rows of acc the calls cover (P, or all d teams' rows with P = Q
 // blocks per row); everything scales with rows x blocks.
 Layout make_layout(int32_t P, int64_t n, int32_t kb, int32_t rows = 0) {
   Layout L;
-  if (rows <= 0) rows = P;
+  const bool one_team = rows <= 0;
+  if (one_team) rows = P;
   const int32_t l = steps_of(P);
   int64_t mmax = 0;   // largest bag over the steps (step 1 is not always the largest)
   for (int32_t i = 1; i <= l; ++i) mmax = std::max<int64_t>(mmax, bag_of(P, l, i));
@@ -96,6 +114,10 @@ Layout make_layout(int32_t P, int64_t n, int32_t kb, int32_t rows = 0) {
   for (int32_t i = 1; i <= l; ++i) L.dtile_pairs += (int64_t)rows * bag_of(P, l, i);
   L.dtile = off;
   off += align256((size_t)L.dtile_pairs * L.add_tiles * 8);
+  // a collection in kernels before the next add: the selected indices of every (worker, block)
+  L.sel = off;
+  L.has_sel = one_team && !collect_in_add(P, n, kb, l);
+  if (L.has_sel) off += align256((size_t)P * P * kb * 4);
   L.fixed_end = off;
   return L;
 }
@@ -142,6 +164,7 @@ struct Ws {
   uint32_t *err, *bitmap, *hist1, *spec_t1, *spec_used, *spec_cnt, *state, *slot_cnt, *slot_nbin, *pre_all, *pre_ge,
       *pre_eq, *keep;
   uint2* dtile;
+  int32_t* sel;   // null if the layout has none
   int32_t* cand_idx;
   float* cand_val;
   uint32_t* bin_key;
@@ -165,27 +188,12 @@ Ws carve(void* ws, size_t ws_bytes, const Layout& L) {
   w.pre_eq = at(L.pre_eq);
   w.keep = at(L.keep);
   w.dtile = (uint2*)at(L.dtile);
+  w.sel = L.has_sel ? (int32_t*)at(L.sel) : nullptr;
   const size_t q = ws_bytes > L.fixed_end ? ((ws_bytes - L.fixed_end) / 3) & ~(size_t)255 : 0;
   w.cand_idx = (int32_t*)(w.base + L.fixed_end);
   w.cand_val = (float*)(w.base + L.fixed_end + q);
   w.bin_key = at(L.fixed_end + 2 * q);
   return w;
-}
-
-// Whether the add that follows a step applies that step's residual collection
-// to its tiles (k_residual_add4 with COLL); otherwise the collection's own
-// kernels run before the plain add, with the same results.  In the tiles it
-// costs time per element streamed, on its own time per entry selected or
-// dropped, scattered, and a launch per SRS step, so it goes into the add for
-// small steps and dense ones.  Whole steps, in the add and apart: P = 8, n =
-// 25.6M at 1 % 619 and 617 us; n = 138M at 0.5 % 2822 and 2672; P = 16, n =
-// 110M at 1 % 4489 and 4394; P = 14, n = 20,033,001 at 1 % 856 and 822; P =
-// 4, n = 50M at 0.1 % 584 and 566, at 1.5 % 677 and 677; but P = 8, n = 8.4M
-// at 1 % 282 and 288, at 0.3 % 243 and 251; P = 6, n = 15M at 10 % 571 and
-// 603.
-bool collect_in_add(int32_t P, int64_t n, int32_t kb, int32_t l) {
-  if (l > COLLECT_MAX_STEPS) return false;   // more SRS steps than the add takes
-  return (int64_t)P * n < (1ll << 27) || 64ll * kb * P > n;
 }
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -283,6 +291,9 @@ struct Fill {
 int topk_units(const float* acc, int64_t ld_acc, int64_t units, const Units& U, int64_t n, int32_t P, int32_t k_blk,
                bool make_hist, bool spec, int32_t* sp_idx, float* sp_val, int32_t* local_idx, const Ws& w,
                const Layout& L, hipStream_t stream, int64_t hint_off = 0, bool keep_rule = false) {
+  // for the residual collection of this step: the selection rule and, if it may run before the next add, the indices
+  uint32_t* const keep = keep_rule ? w.keep + hint_off * KEEP_WORDS : nullptr;
+  int32_t* const sel = keep_rule && w.sel ? w.sel + hint_off * k_blk : nullptr;
   const int32_t smax = (int32_t)L.tiles_tk;
   if (make_hist) {
     SPARDL_TRY(launch_fill(Fill().add(w.hist1, units * L.hcopies * NB1).r, stream));
@@ -302,8 +313,7 @@ int topk_units(const float* acc, int64_t ld_acc, int64_t units, const Units& U, 
   if (one) {
     SPARDL_TRY(launch_topk_one(acc, ld_acc, units, U, n, P, k_blk, smax, (int32_t)L.add_tiles, spec, w.hist1, w.state,
                                hint, w.spec_used, w.spec_cnt, w.slot_cnt, w.slot_nbin, w.cand_idx, w.cand_val, w.bin_key,
-                               sp_idx, sp_val, local_idx, keep_rule ? w.keep + hint_off * KEEP_WORDS : nullptr, w.err,
-                               stream));
+                               sp_idx, sp_val, local_idx, keep, sel, w.err, stream));
     return SPARDL_OK;
   }
   // hist1: the staged threshold for long units builds its level-2/3 histograms in the units'
@@ -312,7 +322,7 @@ int topk_units(const float* acc, int64_t ld_acc, int64_t units, const Units& U, 
                            w.slot_nbin, w.bin_key, w.pre_all, w.pre_ge, w.pre_eq, nullptr, w.err, stream));
   SPARDL_TRY(launch_emit(0, w.cand_idx, w.cand_val, units, U, n, P, k_blk, Pairs{}, smax, w.state, w.slot_cnt,
                          w.pre_all, w.pre_ge, w.pre_eq, sp_idx, sp_val, local_idx, nullptr, nullptr, w.err, stream,
-                         keep_rule ? w.keep + hint_off * KEEP_WORDS : nullptr));
+                         keep, sel));
   return SPARDL_OK;
 }
 
@@ -533,7 +543,9 @@ int spardl_residual_add_collect(float* acc, int64_t ld_acc, const float* grad, i
   sp.cand_idx = w.cand_idx;
   sp.cand_val = w.cand_val;
   if (!collect_in_add(P, n, k_blk, l)) {
-    SPARDL_TRY(launch_grc_zero(acc, ld_acc, nworkers, P, n, k_blk, local_idx, member, stream));
+    // the selected indices as spardl_block_topk kept them in ws (local_idx is not read: a caller need not have
+    // left it as it was)
+    SPARDL_TRY(launch_grc_zero(acc, ld_acc, nworkers, P, n, k_blk, w.sel + (int64_t)w0 * P * k_blk, member, stream));
     for (int32_t i = 1; i <= l; ++i) {
       const int32_t m = bag_of(P, l, i);
       const int64_t skip = (int64_t)w0 * m;   // the pairs of the rows before w0

@@ -1516,7 +1516,8 @@ __global__ __launch_bounds__(1024) void k_big_scan(BigArgs a) {
 // MODE 0 (block top-k): few candidates per slot, one wave per slot, or SPW
 // consecutive slots per wave when the call has many slots (as the collect),
 // with the counts, prefixes and first entries of all of them loaded before
-// any is emitted; no LDS and no barrier; selected -> sp (and local_idx).
+// any is emitted; no LDS and no barrier; selected -> sp (and
+// local_idx, and sel, the workspace's copy).
 // MODE 1 (merge): slots are full merge tiles, so a workgroup takes one slot
 // and each wave a quarter of it, the counts of the quarters before it
 // exchanged through LDS; selected -> sp[w][b] in place, the rest -> the
@@ -1534,8 +1535,8 @@ __device__ __forceinline__ void emit_topk_slot(uint32_t cnt, uint32_t run_g, uin
                                                const int32_t* __restrict__ CI, const float* __restrict__ CV,
                                                const int32_t (&ix1)[R1], const float (&vx1)[R1],
                                                int32_t* __restrict__ oI, float* __restrict__ oV,
-                                               int32_t* __restrict__ oL, uint32_t* __restrict__ err,
-                                               uint32_t* __restrict__ kcut) {
+                                               int32_t* __restrict__ oL, int32_t* __restrict__ oS,
+                                               uint32_t* __restrict__ err, uint32_t* __restrict__ kcut) {
   const int lane = lane_id();
   const uint64_t lt = __lanemask_lt();
   auto put = [&](uint32_t p, int32_t ix, float vx) {
@@ -1552,6 +1553,7 @@ __device__ __forceinline__ void emit_topk_slot(uint32_t cnt, uint32_t run_g, uin
         oI[sel_before] = ix;
         oV[sel_before] = vx;
         if (oL) oL[sel_before] = ix;
+        if (oS) oS[sel_before] = ix;
       } else {
         atomicOr(err, ERR_COUNT_POS);
       }
@@ -1587,7 +1589,8 @@ __global__ __launch_bounds__(256) void k_emit(
     const uint32_t* __restrict__ slot_cnt, const uint32_t* __restrict__ pre_all,
     const uint32_t* __restrict__ pre_ge, const uint32_t* __restrict__ pre_eq, int32_t* __restrict__ out_idx,
     float* __restrict__ out_val, int32_t* __restrict__ local_idx, int32_t* __restrict__ drop_idx,
-    float* __restrict__ drop_val, uint32_t* __restrict__ err, uint32_t* __restrict__ keep) {
+    float* __restrict__ drop_val, uint32_t* __restrict__ err, uint32_t* __restrict__ keep,
+    int32_t* __restrict__ sel) {
   const uint32_t unit = blockIdx.x / gq;
   const int wv = wave_id();
   if constexpr (MODE == 0 && SPW == 1) {
@@ -1644,6 +1647,7 @@ __global__ __launch_bounds__(256) void k_emit(
               out_idx[o + sel_before] = ix[r];
               out_val[o + sel_before] = vx[r];
               if (local_idx) local_idx[o + sel_before] = ix[r];
+              if (sel) sel[o + sel_before] = ix[r];
             } else {
               atomicOr(err, ERR_COUNT_POS);
             }
@@ -1707,7 +1711,7 @@ __global__ __launch_bounds__(256) void k_emit(
       if (sw + j >= g.nslots) break;   // wave-uniform
       const int64_t base = g.base + g.off(sw + j);
       emit_topk_slot<R1>(cnt[j], rg[j], re[j], tge, teq, need_eq, kb, cand_idx + base, cand_val + base, ix[j], vx[j],
-                     out_idx + o, out_val + o, local_idx ? local_idx + o : nullptr, err,
+                     out_idx + o, out_val + o, local_idx ? local_idx + o : nullptr, sel ? sel + o : nullptr, err,
                      kp ? kp + KEEP_CUT : nullptr);
     }
   } else {
@@ -1861,7 +1865,7 @@ struct TopkOne {
   const uint32_t *spec_used, *spec_cnt, *slot_cnt, *slot_nbin, *bin_key;
   int32_t* cand_idx;
   float* cand_val;
-  int32_t *out_idx, *local_idx;
+  int32_t *out_idx, *local_idx, *sel;
   float* out_val;
 };
 
@@ -2231,6 +2235,7 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
     a.out_idx[out + i] = oi[i];
     a.out_val[out + i] = ov[i];
     if (a.local_idx) a.local_idx[out + i] = oi[i];
+    if (a.sel) a.sel[out + i] = oi[i];
   }
   if (t == 0) {
     if (taken != a.kb) atomicOr(a.err, ERR_COUNT_SUM);
@@ -2257,7 +2262,7 @@ hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, con
                            uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt,
                            const uint32_t* slot_cnt, const uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val,
                            const uint32_t* bin_key, int32_t* out_idx, float* out_val, int32_t* local_idx,
-                           uint32_t* keep, uint32_t* err, hipStream_t s) {
+                           uint32_t* keep, int32_t* sel, uint32_t* err, hipStream_t s) {
   TopkOne a;
   a.acc = acc;
   a.ld_acc = ld_acc;
@@ -2282,6 +2287,7 @@ hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, con
   a.cand_val = cand_val;
   a.out_idx = out_idx;
   a.local_idx = local_idx;
+  a.sel = sel;
   a.out_val = out_val;
   if (topk_alone(n, P)) hipLaunchKernelGGL(k_topk_one<true>, dim3((unsigned)nunits), dim3(ONE_THREADS), 0, s, a);
   else hipLaunchKernelGGL(k_topk_one<false>, dim3((unsigned)nunits), dim3(ONE_THREADS), 0, s, a);
@@ -2374,20 +2380,21 @@ hipError_t launch_emit(int mode, const int32_t* cand_idx, const float* cand_val,
                        int64_t n, int32_t P, int32_t kb, const Pairs& PM, int32_t smax, const uint32_t* state,
                        const uint32_t* slot_cnt, const uint32_t* pre_all, const uint32_t* pre_ge,
                        const uint32_t* pre_eq, int32_t* out_idx, float* out_val, int32_t* local_idx,
-                       int32_t* drop_idx, float* drop_val, uint32_t* err, hipStream_t s, uint32_t* keep) {
+                       int32_t* drop_idx, float* drop_val, uint32_t* err, hipStream_t s, uint32_t* keep,
+                       int32_t* sel) {
   // block top-k: 4 spw slots per workgroup (spw per wave); merge: one slot per workgroup
   const int spw = mode == 0 ? topk_slots_per_wave(nunits, smax, kb) : 1;
   const uint32_t gq = mode == 0 ? (uint32_t)((smax + 4 * spw - 1) / (4 * spw)) : (uint32_t)smax;
   const dim3 grid((unsigned)(nunits * gq));
   const Blocks B = make_blocks(n, P);
   if (mode == 0 && spw == 8)
-    hipLaunchKernelGGL((k_emit<0, 8>), grid, dim3(256), 0, s, cand_idx, cand_val, B, U, PM, kb, smax, gq, state, slot_cnt, pre_all, pre_ge, pre_eq, out_idx, out_val, local_idx, drop_idx, drop_val, err, keep);
+    hipLaunchKernelGGL((k_emit<0, 8>), grid, dim3(256), 0, s, cand_idx, cand_val, B, U, PM, kb, smax, gq, state, slot_cnt, pre_all, pre_ge, pre_eq, out_idx, out_val, local_idx, drop_idx, drop_val, err, keep, sel);
   else if (mode == 0 && spw == 2)
-    hipLaunchKernelGGL((k_emit<0, 2>), grid, dim3(256), 0, s, cand_idx, cand_val, B, U, PM, kb, smax, gq, state, slot_cnt, pre_all, pre_ge, pre_eq, out_idx, out_val, local_idx, drop_idx, drop_val, err, keep);
+    hipLaunchKernelGGL((k_emit<0, 2>), grid, dim3(256), 0, s, cand_idx, cand_val, B, U, PM, kb, smax, gq, state, slot_cnt, pre_all, pre_ge, pre_eq, out_idx, out_val, local_idx, drop_idx, drop_val, err, keep, sel);
   else if (mode == 0)
-    hipLaunchKernelGGL(k_emit<0>, grid, dim3(256), 0, s, cand_idx, cand_val, B, U, PM, kb, smax, gq, state, slot_cnt, pre_all, pre_ge, pre_eq, out_idx, out_val, local_idx, drop_idx, drop_val, err, keep);
+    hipLaunchKernelGGL(k_emit<0>, grid, dim3(256), 0, s, cand_idx, cand_val, B, U, PM, kb, smax, gq, state, slot_cnt, pre_all, pre_ge, pre_eq, out_idx, out_val, local_idx, drop_idx, drop_val, err, keep, sel);
   else
-    hipLaunchKernelGGL(k_emit<1>, grid, dim3(256), 0, s, cand_idx, cand_val, B, U, PM, kb, smax, gq, state, slot_cnt, pre_all, pre_ge, pre_eq, out_idx, out_val, local_idx, drop_idx, drop_val, err, keep);
+    hipLaunchKernelGGL(k_emit<1>, grid, dim3(256), 0, s, cand_idx, cand_val, B, U, PM, kb, smax, gq, state, slot_cnt, pre_all, pre_ge, pre_eq, out_idx, out_val, local_idx, drop_idx, drop_val, err, keep, sel);
   return hipGetLastError();
 }
 

@@ -69,7 +69,7 @@ hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, con
                            uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt,
                            const uint32_t* slot_cnt, const uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val,
                            const uint32_t* bin_key, int32_t* out_idx, float* out_val, int32_t* local_idx,
-                           uint32_t* keep, uint32_t* err, hipStream_t s);
+                           uint32_t* keep, int32_t* sel, uint32_t* err, hipStream_t s);
 hipError_t launch_collect(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
                           int32_t kb, int32_t smax, const uint32_t* state, const uint32_t* spec_cnt,
                           int32_t add_tiles, uint32_t* slot_cnt, uint32_t* slot_nbin, int32_t* cand_idx,
@@ -82,7 +82,8 @@ hipError_t launch_emit(int mode, const int32_t* cand_idx, const float* cand_val,
                        int64_t n, int32_t P, int32_t kb, const Pairs& PM, int32_t smax, const uint32_t* state,
                        const uint32_t* slot_cnt, const uint32_t* pre_all, const uint32_t* pre_ge,
                        const uint32_t* pre_eq, int32_t* out_idx, float* out_val, int32_t* local_idx,
-                       int32_t* drop_idx, float* drop_val, uint32_t* err, hipStream_t s, uint32_t* keep = nullptr);
+                       int32_t* drop_idx, float* drop_val, uint32_t* err, hipStream_t s, uint32_t* keep = nullptr,
+                       int32_t* sel = nullptr);
 // Union tiles and their level-1 histogram; with merge_fine(kb) the fine window
 // (its first bin in the pairs' state word ST_WBASE) and, per slot, the keys'
 // low bits in bin order and the bins' prefix in the slot's words of U_key.

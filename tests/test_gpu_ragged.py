@@ -108,3 +108,26 @@ def test_unsorted_drops_are_reported(n, kb):
     st.drop_idx[0][0, 0, :2] = st.drop_idx[0][0, 0, :2].flip(0)
     spardl.residual_collect_index(0, P, n, P, kb, st.drop_idx, st.drop_cnt, st.ws)
     assert spardl.ws_error(st.ws) & 64, "ERR_DROPS"
+
+
+# in the add's tiles; before the add: the top-k ended by one workgroup, by the general emit (a slot, 2 and 8 per wave)
+@pytest.mark.parametrize("P,n,kb", [(2, 2 ** 22, 1000), (64, 2 ** 21 + 64, 30), (2, 2 ** 26, 5000), (2, 2 ** 26 + 3, 100_000),
+                                    (4, 2 ** 28, 1_000_000), (2, 2 ** 29, 40_000)])
+@pytest.mark.parametrize("rows", [0, 1])
+def test_deferred_collection_does_not_read_local_idx(P, n, kb, rows):
+    """A caller may reuse local_idx once a step is done: spoiled here between
+    two steps, the residual is that of a collection as its own call."""
+    log(f"local_idx spoiled before a deferred collection P={P} n={n} kb={kb} rows={rows}")
+    deferred = spardl.SparDLStep(P, n, kb, rows_per_call=rows, fuse_collect=True)
+    own = spardl.SparDLStep(P, n, kb, rows_per_call=rows)
+    gen = torch.Generator(device="cuda").manual_seed(n + kb)
+    grad = torch.empty((P, n), device="cuda")
+    for t in range(3):
+        grad.normal_(generator=gen)
+        deferred.local_idx.fill_(-1)
+        for st in (deferred, own):
+            st.step(grad)
+            check_ws(st)
+        assert torch.equal(deferred.dense, own.dense), f"update of step {t + 1}"
+    deferred.flush()
+    assert torch.equal(deferred.acc.view(torch.int32), own.acc.view(torch.int32)), "residual"
