@@ -48,20 +48,24 @@ struct Layout {
   int64_t units = 0, tiles_tk = 0, tiles_mg = 0, slot_n = 0, pairs_max = 0, add_tiles = 0;
 };
 
-// Whether the add that follows a step applies that step's residual collection
-// to its tiles (k_residual_add4 with COLL); otherwise the collection's own
-// kernels run before the plain add, with the same results.  In the tiles it
-// costs time per element streamed, on its own time per entry selected or
-// dropped, scattered, and a launch per SRS step, so it goes into the add for
-// small steps and dense ones.  Whole steps, in the add and apart: P = 8, n =
-// 25.6M at 1 % 619 and 617 us; n = 138M at 0.5 % 2822 and 2672; P = 16, n =
-// 110M at 1 % 4489 and 4394; P = 14, n = 20,033,001 at 1 % 856 and 822; P =
-// 4, n = 50M at 0.1 % 584 and 566, at 1.5 % 677 and 677; but P = 8, n = 8.4M
-// at 1 % 282 and 288, at 0.3 % 243 and 251; P = 6, n = 15M at 10 % 571 and
-// 603.
-bool collect_in_add(int32_t P, int64_t n, int32_t kb, int32_t l) {
+// Whether an add over nworkers rows applies the previous step's residual
+// collection to its tiles (k_residual_add4 with COLL); otherwise the
+// collection's own kernels run before the plain add, with the same results.
+// In the tiles it costs time per element streamed, on its own a launch per SRS
+// step and one more, and time per entry selected or dropped, scattered: so it
+// goes into the add for calls of fewer than 8M elements per SRS step, and for
+// dense ones.  Whole steps in us, in the tiles and apart, all rows in one call:
+// P = 2, 0.1 %, n = 4M 75 and 78, 8M 121 and 117; P = 4, 0.1 %, n = 4M 99 and
+// 100, 8M 155 and 152; P = 8, 1 %, n = 2M 126 and 130, 4M 204 and 200, 25.6M
+// 679 and 646; P = 16, 1 %, n = 1M 110 and 118, 2M 167 and 167, 4M 266 and 249.
+// One row per call: P = 8, n = 25.6M at 1 % 1040 and 1019; P = 16, n = 30M at
+// 1 % 2043 and 2091, 60M at 0.1 % 3008 and 2907; P = 32, n = 40M at 0.1 % 3858
+// and 3955 (two rows 3351 and 3268).  Densities of 1.6, 3 and 10 %: P = 4, n =
+// 32M 521 and 494, 578 and 578, 905 and 979; P = 16, n = 4M 292 and 276, 347 and
+// 334, 471 and 517; P = 2, n = 64M at 0.1 and 1 % 425 and 413, 474 and 487.
+bool collect_in_add(int32_t nworkers, int32_t P, int64_t n, int32_t kb, int32_t l) {
   if (l > COLLECT_MAX_STEPS) return false;   // more SRS steps than the add takes
-  return (int64_t)P * n < (1ll << 27) || 64ll * kb * P > n;
+  return (int64_t)nworkers * n < (int64_t)std::max(l, 1) << 23 || (l > 1 ? 64ll : 128ll) * kb * P > n;
 }
 
 // rows: rows of acc the calls cover (P, or all d teams' rows with P = Q
@@ -116,7 +120,7 @@ Layout make_layout(int32_t P, int64_t n, int32_t kb, int32_t rows = 0) {
   off += align256((size_t)L.dtile_pairs * L.add_tiles * 8);
   // a collection in kernels before the next add: the selected indices of every (worker, block)
   L.sel = off;
-  L.has_sel = one_team && !collect_in_add(P, n, kb, l);
+  L.has_sel = one_team && !collect_in_add(P, P, n, kb, l);
   if (L.has_sel) off += align256((size_t)P * P * kb * 4);
   L.fixed_end = off;
   return L;
@@ -542,7 +546,7 @@ int spardl_residual_add_collect(float* acc, int64_t ld_acc, const float* grad, i
   sp.spec_cnt = w.spec_cnt;
   sp.cand_idx = w.cand_idx;
   sp.cand_val = w.cand_val;
-  if (!collect_in_add(P, n, k_blk, l)) {
+  if (!collect_in_add(nworkers, P, n, k_blk, l)) {
     // the selected indices as spardl_block_topk kept them in ws (local_idx is not read: a caller need not have
     // left it as it was)
     SPARDL_TRY(launch_grc_zero(acc, ld_acc, nworkers, P, n, k_blk, w.sel + (int64_t)w0 * P * k_blk, member, stream));

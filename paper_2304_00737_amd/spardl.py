@@ -375,7 +375,7 @@ def ws_layout(P: int, n: int, kb: int, ws_bytes: int) -> dict:
     L["keep"] = off; off += al(P * P * 4 * 4)             # the block top-k's selection rule per (worker, block)
     L["dtile"] = off; off += al(sum(P * m for m in bags) * add_tiles * 8)   # per (step, pair, add tile)
     L["sel"] = off                                        # the selected indices, where the residual collection may
-    if P * n >= 1 << 27 and 64 * kb * P <= n:             # run in kernels before the next add
+    if P * n >= max(l, 1) << 23 and (64 if l > 1 else 128) * kb * P <= n:   # run in kernels before the next add
         off += al(P * P * kb * 4)
     L["fixed_end"] = off
     L["cand_entries"] = max(P * n, pairs_max * tiles_mg * 4096)

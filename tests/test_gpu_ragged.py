@@ -93,6 +93,33 @@ def test_collection_in_the_add_or_before_it(n, kb, rows):
     assert torch.equal(deferred.acc.view(torch.int32), own.acc.view(torch.int32)), "residual"
 
 
+# P, n, kb, rows per call: calls of 8M elements per SRS step, one less and a few more; densities of 1/128 (one SRS
+# step) and 1/64 and just above; rows a few at a time on both sides, an uneven last group in the tiles and the others not
+@pytest.mark.parametrize("P,n,kb,rows", [(2, 2 ** 22, 1000, 0), (2, 2 ** 22 - 1, 1000, 0), (2, 2 ** 22 + 1, 1000, 0),
+                                         (2, 2 ** 22, 2 ** 14, 0), (2, 2 ** 22, 2 ** 14 + 1, 0), (4, 2 ** 22, 1000, 0),
+                                         (4, 2 ** 22, 2 ** 14, 0), (4, 2 ** 22, 2 ** 14 + 1, 0), (4, 2 ** 22, 1000, 1),
+                                         (4, 2 ** 24, 1000, 1), (3, 2 ** 23, 1000, 2), (1, 2 ** 23, 9000, 0)])
+def test_collection_in_the_add_or_before_it_by_rows(P, n, kb, rows):
+    """The route of the deferred collection follows the rows of the call (its
+    index is built for all of them): the same steps as with the collection as
+    its own call."""
+    log(f"collection in the add or before it P={P} n={n} kb={kb} rows={rows}")
+    deferred = spardl.SparDLStep(P, n, kb, rows_per_call=rows, fuse_collect=True)
+    own = spardl.SparDLStep(P, n, kb, rows_per_call=rows)
+    gen = torch.Generator(device="cuda").manual_seed(n + kb)
+    grad = torch.empty((P, n), device="cuda")
+    for t in range(3):
+        grad.normal_(generator=gen)
+        for st in (deferred, own):
+            st.step(grad)
+            check_ws(st)
+        assert torch.equal(deferred.dense, own.dense), f"update of step {t + 1}"
+        assert torch.equal(deferred.local_idx, own.local_idx), f"selections of step {t + 1}"
+    deferred.flush()
+    check_ws(deferred)
+    assert torch.equal(deferred.acc.view(torch.int32), own.acc.view(torch.int32)), "residual"
+
+
 # the collection in the add's tiles; before the add, even and ragged rows
 @pytest.mark.parametrize("n,kb", [(4096, 40), (2 ** 26, 1000), (2 ** 26 + 3, 1000)])
 def test_unsorted_drops_are_reported(n, kb):
