@@ -1834,18 +1834,19 @@ __global__ __launch_bounds__(256) void k_emit(
 // to this kernel: a wave per slot of a few entries each costs more than this
 // one's longer list searches there (256 blocks of 1M 54 us collected and 37
 // taken as they are, 32 of 1.25M 29 and 28; but 16 of 2^18 25.8 and 26.4, 4 of
-// 2M 22.3 and 24.2).  Against k_thresh and k_emit: 29 and 26 us for 16 blocks
-// of 2^18 at 1 %, 106 and 37 us for 256 of 1M at 0.1 %, 39 and 28 us for 32 of
-// 1.25M at 0.1 %, 26 and 22 us for 4 of 2M at 0.05 %.
+// 2M 22.3 and 24.2).  Against k_thresh and k_emit: 29 and 23 us for 16 blocks
+// of 2^18 at 1 %, 106 and 35 us for 256 of 1M at 0.1 %, 39 and 25 us for 32 of
+// 1.25M at 0.1 %, 26 and 21 us for 4 of 2M at 0.05 %.
 //
 // Bound by the chain of barriers and by one CU's instruction issue (an entry's
-// list is found by 7 to 10 LDS reads), which is why it ends at ONE_KB entries.
-// Where ties or zeros leave more candidates than the registers hold, ALONE
-// loads them again in at most four chunks per pass, and in long blocks every
-// wave walks whole slots, in both with one LDS add for the lanes that agree on
-// a bin: 4 blocks of 2M zeros with fewer than kb other entries take 1.3 ms,
-// against 8.8 by k_thresh and k_emit and 10.6 by this kernel with a list search
-// and an LDS add per entry.
+// list is found by 7 to 10 LDS reads) and fetch, which is why it ends at ONE_KB
+// entries and has one form of every loop: a second one for more candidates than
+// the registers hold, which walked a slot per wave, made 22.5 us of 26.  Where
+// ties or zeros leave so many they are loaded again in chunks, a pass each for
+// levels 2, 3 and the emit (ALONE: level 1 too), the lanes that agree on a bin
+// adding to it once: 4 blocks of 2M zeros with fewer than kb other entries take
+// 5.6 ms (8.8 by k_thresh and k_emit, 10.6 with an LDS add per entry), 16 blocks
+// of 65536 0.16 (0.25, 0.29).
 constexpr int ONE_THREADS = 1024;
 constexpr int ONE_R = 16;                            // candidates per thread in registers
 constexpr int ONE_CAP = ONE_THREADS * ONE_R;         // a chunk
@@ -1902,7 +1903,6 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
   uint32_t pfx = 0u, cnt = 0u, need = 0u;
   int S = FINE_SHIFT;
   bool specok = false;                                 // ALONE: the add's candidates decide
-  uint32_t cs = 0u, bs = 0u;                           // not the add's lists: thread t's slot: its entries, those in the bin
   if constexpr (ALONE) {
     uint32_t* __restrict__ H = a.hist1 + u * a.hc * NB1;
     used = a.spec ? a.spec_used[u] : SPEC_NONE;
@@ -1963,6 +1963,7 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
     } else {
       lw = (uint32_t)SLOT;
       nl = (e - o + lw - 1u) / lw;
+      uint32_t cs = 0u, bs = 0u;   // thread t's slot: its entries and those in the bin
       if (t < nl) {
         const uint32_t x0 = o + t * lw;
         cs = min(a.slot_cnt[u * a.smax + t], min(x0 + lw, e) - max(x0, s));
@@ -2016,9 +2017,7 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
       }
     }
   };
-  // !ALONE with more candidates than the registers hold: each wave walks whole slots
-  const bool walk = !ALONE && nch > 1u;   // uniform
-  if (nch > 0u && !walk) load(0u);
+  if (nch > 0u) load(0u);
 
   // ---- ALONE: level 1 in bins of 2^FINE_SHIFT keys from the smallest candidate key on, the last also holding
   // every larger key; if the threshold falls there, bins of the top 12 key bits
@@ -2073,161 +2072,65 @@ __global__ __launch_bounds__(ONE_THREADS) void k_topk_one(TopkOne a) {
     if (!ok) cnt = 0u;
     if (t == 0 && a.spec_t1) a.spec_t1[u] = ok ? ((pfx << S) >> D1_SHIFT) + 1u : 0u;   // the next add's floor: 12-bit bins
   }
-  // thread t's slot in LDS: its entries and those in the bin, later the counts before it
-  __shared__ uint32_t sc[ALONE ? 1 : ONE_LISTS], sb[ALONE ? 1 : ONE_LISTS], sg[ALONE ? 1 : ONE_LISTS],
-      se[ALONE ? 1 : ONE_LISTS];
-  const int lane = lane_id(), wv = wave_id();
-  // f(key, live) for the threshold-bin keys of slot i, a wave's 64 at a time
-  auto slot_bin = [&](uint32_t i, auto f) {
-    const uint32_t* __restrict__ K = a.bin_key + (int64_t)w * a.B.n + max(o + i * lw, s);
-    const uint32_t c = sb[i];
-    constexpr int R = 8;
-    for (uint32_t p0 = 0; p0 < c; p0 += WAVE * R) {
-      uint32_t k[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const uint32_t p = p0 + (uint32_t)(r * WAVE + lane);
-        k[r] = p < c ? K[p] : 0u;
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) f(k[r], p0 + (uint32_t)(r * WAVE + lane) < c);
-    }
-  };
-  if (walk) {
-    if (t < nl) {
-      sc[t] = cs;
-      sb[t] = bs;
-    }
-    __syncthreads();
-  }
   uint32_t tge, teq, need_eq;
   resolve_bin(pfx, S, need, cnt, h, scratch, a.err,
               [&](auto f) {
-                if (walk) {
-                  for (uint32_t i = (uint32_t)wv; i < nl; i += NWV)
-                    slot_bin(i, [&](uint32_t key, bool live) {
-                      if (live && (key >> S) == pfx) f(key);
-                    });
-                } else {
-                  each([&](uint32_t key) {
-                    if ((key >> S) == pfx) f(key);
-                  });
-                }
+                each([&](uint32_t key) {
+                  if ((key >> S) == pfx) f(key);
+                });
               },
               tge, teq, need_eq, same);
 
   // ---- emit in index order: an entry's place is the entries >= TGE before it plus the ties taken before
   // it; staged in LDS, then written as whole lines
+  const int lane = lane_id(), wv = wave_id();
   const uint64_t lt = __lanemask_lt();
   int32_t* oi = reinterpret_cast<int32_t*>(h);
   uint32_t run_g = 0u, run_e = 0u;
   __syncthreads();   // the histogram's space is read no more
-  // a wave's 64 entries, gp entries >= TGE and ep ties before them
-  auto put = [&](int32_t i, float v, uint64_t mg, uint64_t me, bool is_ge, bool is_eq, uint32_t gp, uint32_t ep) {
-    gp += popc64(mg & lt);
-    ep += popc64(me & lt);
-    if (a.keep && is_eq && ep + 1u == need_eq) a.keep[u * KEEP_WORDS + KEEP_CUT] = (uint32_t)i;   // the last tie taken
-    if (is_ge || (is_eq && ep < need_eq)) {
-      const uint32_t pos = gp + min(ep, need_eq);
-      if (pos < a.kb) {
-        oi[pos] = i;
-        ov[pos] = v;
-      } else {
-        atomicOr(a.err, ERR_COUNT_POS);
-      }
-    }
-  };
-  if (walk) {
-    // per slot the entries selected by key and the ties: those above the bin, and the bin's
-    for (uint32_t i = (uint32_t)wv; i < nl; i += NWV) {
-      uint32_t g = sc[i] - sb[i], q = 0u;
-      slot_bin(i, [&](uint32_t key, bool live) {
-        g += popc64(__ballot(live && key >= tge));
-        q += popc64(__ballot(live && need_eq != 0u && key == teq));
-      });
-      if (lane == 0) {
-        sg[i] = g;
-        se[i] = q;
-      }
-    }
-    __syncthreads();
-    const uint32_t g = t < nl ? sg[t] : 0u, q = t < nl ? se[t] : 0u;
-    uint32_t x3[3] = {g, q, 0u}, t3[3];
-    block_excl_scan3(x3, scratch, t3);
-    run_g = t3[0];
-    run_e = t3[1];
-    if (t < nl) {
-      sg[t] = x3[0];
-      se[t] = x3[1];
-      if (g == 0u && (q == 0u || x3[1] >= need_eq)) sc[t] = 0u;   // nothing of the slot is selected
-    }
-    __syncthreads();
-    for (uint32_t i = (uint32_t)wv; i < nl; i += NWV) {
-      const uint32_t c = sc[i];
-      const int64_t at = max(o + i * lw, s);
-      uint32_t gp = sg[i], ep = se[i];
-      constexpr int R = 8;
-      for (uint32_t p0 = 0; p0 < c; p0 += WAVE * R) {
-        int32_t i1[R];
-        float v1[R];
+  for (uint32_t c = 0; c < nch; ++c) {
+    if (nch > 1u) load(c);   // uniform
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const uint32_t p = p0 + (uint32_t)(r * WAVE + lane);
-          i1[r] = 0;
-          v1[r] = 0.f;
-          if (p < c) {
-            i1[r] = CI[at + p];
-            v1[r] = CV[at + p];
+    for (int r = 0; r < ONE_R; ++r) {
+      if ((uint32_t)r < per) {   // uniform
+        const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
+        const uint32_t key = mag_key(vx[r]);
+        const uint32_t g = popc64(__ballot(live && key >= tge));
+        const uint32_t q = popc64(__ballot(live && need_eq != 0u && key == teq));
+        if (lane == 0) cw[(uint32_t)r * NWV + (uint32_t)wv] = g | (q << 16);
+      }
+    }
+    __syncthreads();
+    static_assert(ONE_CAP < (1 << 16), "packed counts of a chunk");
+    uint32_t tot;
+    const uint32_t mine = t < per * NWV ? cw[t] : 0u;
+    const uint32_t before = block_excl_scan(mine, scratch, &tot);
+    if (t < per * NWV) cw[t] = before;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ONE_R; ++r) {
+      if ((uint32_t)r < per) {   // uniform
+        const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
+        const uint32_t key = mag_key(vx[r]);
+        const bool is_ge = live && key >= tge, is_eq = live && need_eq != 0u && key == teq;
+        const uint64_t mg = __ballot(is_ge), me = __ballot(is_eq);
+        const uint32_t x = cw[(uint32_t)r * NWV + (uint32_t)wv];
+        const uint32_t gp = run_g + (x & 0xFFFFu) + popc64(mg & lt), ep = run_e + (x >> 16) + popc64(me & lt);
+        if (a.keep && is_eq && ep + 1u == need_eq) a.keep[u * KEEP_WORDS + KEEP_CUT] = (uint32_t)ix[r];   // the last tie taken
+        if (is_ge || (is_eq && ep < need_eq)) {
+          const uint32_t pos = gp + min(ep, need_eq);
+          if (pos < a.kb) {
+            oi[pos] = ix[r];
+            ov[pos] = vx[r];
+          } else {
+            atomicOr(a.err, ERR_COUNT_POS);
           }
         }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const bool live = p0 + (uint32_t)(r * WAVE + lane) < c;
-          const uint32_t key = mag_key(v1[r]);
-          const bool is_ge = live && key >= tge, is_eq = live && need_eq != 0u && key == teq;
-          const uint64_t mg = __ballot(is_ge), me = __ballot(is_eq);
-          put(i1[r], v1[r], mg, me, is_ge, is_eq, gp, ep);
-          gp += popc64(mg);
-          ep += popc64(me);
-        }
       }
     }
-    __syncthreads();   // the staged selection is complete
-  } else {
-    for (uint32_t c = 0; c < nch; ++c) {
-      if (nch > 1u) load(c);   // uniform
-#pragma unroll
-      for (int r = 0; r < ONE_R; ++r) {
-        if ((uint32_t)r < per) {   // uniform
-          const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
-          const uint32_t key = mag_key(vx[r]);
-          const uint32_t g = popc64(__ballot(live && key >= tge));
-          const uint32_t q = popc64(__ballot(live && need_eq != 0u && key == teq));
-          if (lane == 0) cw[(uint32_t)r * NWV + (uint32_t)wv] = g | (q << 16);
-        }
-      }
-      __syncthreads();
-      static_assert(ONE_CAP < (1 << 16), "packed counts of a chunk");
-      uint32_t tot;
-      const uint32_t mine = t < per * NWV ? cw[t] : 0u;
-      const uint32_t before = block_excl_scan(mine, scratch, &tot);
-      if (t < per * NWV) cw[t] = before;
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < ONE_R; ++r) {
-        if ((uint32_t)r < per) {   // uniform
-          const bool live = e0 + (uint32_t)(r * ONE_THREADS) < N;
-          const uint32_t key = mag_key(vx[r]);
-          const bool is_ge = live && key >= tge, is_eq = live && need_eq != 0u && key == teq;
-          const uint64_t mg = __ballot(is_ge), me = __ballot(is_eq);
-          const uint32_t x = cw[(uint32_t)r * NWV + (uint32_t)wv];
-          put(ix[r], vx[r], mg, me, is_ge, is_eq, run_g + (x & 0xFFFFu), run_e + (x >> 16));
-        }
-      }
-      run_g += tot & 0xFFFFu;
-      run_e += tot >> 16;
-      __syncthreads();   // cw is written again
-    }
+    run_g += tot & 0xFFFFu;
+    run_e += tot >> 16;
+    __syncthreads();   // cw is written again
   }
   const uint32_t taken = run_g + min(run_e, need_eq);
   const int64_t out = u * a.kb;
