@@ -578,7 +578,7 @@ int spardl_residual_collect_index(int32_t w0, int32_t nworkers, int64_t n, int32
   const size_t need = spardl_workspace_bytes(1, P, n, k_blk);
   if (need == 0) return SPARDL_EINVAL;
   if (ws_bytes < need) return SPARDL_ECAPACITY;
-  // the index is built, and the lists with it checked, also where the add will collect by the separate kernels
+  // (the lists are checked also where every add of these sizes collects by the separate kernels)
   if (l == 0 || l > COLLECT_MAX_STEPS) return SPARDL_OK;
   const Layout L = make_layout(P, n, k_blk);
   Ws w = carve(ws, ws_bytes, L);
@@ -587,7 +587,7 @@ int spardl_residual_collect_index(int32_t w0, int32_t nworkers, int64_t n, int32
   // only tiles with drops are written: the add clamps every range to the
   // pair's drop count and takes only entries inside its tile, so a range a
   // tile kept from an earlier step adds nothing
-  SPARDL_TRY(launch_drop_tiles(C, drop_cnt, nworkers, n, P, w.err, stream));
+  SPARDL_TRY(launch_drop_tiles(C, drop_cnt, nworkers, n, P, collect_in_add(1, P, n, k_blk, l), w.err, stream));
   return SPARDL_OK;
 }
 

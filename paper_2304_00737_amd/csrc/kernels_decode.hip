@@ -167,6 +167,9 @@ struct DropTiles {
   uint32_t nw;
 };
 
+// INDEX: false where no add of these sizes reads the index (the lists are then
+// only checked).
+template <bool INDEX>
 __global__ __launch_bounds__(256) void k_drop_tiles(DropTiles D, Blocks B, uint32_t* __restrict__ err) {
   const AddCollect& C = D.C;
   for (uint32_t y = blockIdx.y; y < D.pcum[C.l]; y += gridDim.y) {
@@ -199,6 +202,7 @@ __global__ __launch_bounds__(256) void k_drop_tiles(DropTiles D, Blocks B, uint3
           atomicOr(err, ERR_DROPS);
           continue;
         }
+        if constexpr (!INDEX) continue;
         const uint32_t t = (x - o) / (uint32_t)ADD_TILE;
         const bool first = j == 0u || (xs[u - 1] - o) / (uint32_t)ADD_TILE != t;
         const bool last = j + 1u == cnt || (xs[u + 1] - o) / (uint32_t)ADD_TILE != t;
@@ -274,7 +278,7 @@ hipError_t launch_grc_drops(float* acc, int64_t ld_acc, int64_t n, int32_t m, in
 }
 
 hipError_t launch_drop_tiles(const AddCollect& C, const int32_t* const* drop_cnt, int32_t nw, int64_t n, int32_t P,
-                             uint32_t* err, hipStream_t s) {
+                             bool index, uint32_t* err, hipStream_t s) {
   if (C.l <= 0) return hipSuccess;
   if (C.l > COLLECT_MAX_STEPS) return hipErrorInvalidValue;
   DropTiles D;
@@ -286,7 +290,8 @@ hipError_t launch_drop_tiles(const AddCollect& C, const int32_t* const* drop_cnt
     D.pcum[i + 1] = D.pcum[i] + (uint32_t)nw * C.m[i];
   }
   const dim3 grid(grid_for(((int64_t)C.kb + DT_PER - 1) / DT_PER, 256, 1024), (unsigned)std::min<uint32_t>(D.pcum[C.l], 65535u));
-  hipLaunchKernelGGL(k_drop_tiles, grid, dim3(256), 0, s, D, make_blocks(n, P), err);
+  if (index) hipLaunchKernelGGL(k_drop_tiles<true>, grid, dim3(256), 0, s, D, make_blocks(n, P), err);
+  else hipLaunchKernelGGL(k_drop_tiles<false>, grid, dim3(256), 0, s, D, make_blocks(n, P), err);
   return hipGetLastError();
 }
 

@@ -52,7 +52,7 @@ hipError_t launch_residual_add(float* acc, int64_t ld_acc, const float* grad, in
 // harmlessly (it clamps a range to the pair's drop count and adds only
 // entries inside its tile).
 hipError_t launch_drop_tiles(const AddCollect& C, const int32_t* const* drop_cnt, int32_t nw, int64_t n, int32_t P,
-                             uint32_t* err, hipStream_t s);
+                             bool index, uint32_t* err, hipStream_t s);
 // Block top-k stages over nunits selection units (Units in common.hpp).
 hipError_t launch_hist1(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
                         uint32_t* hist1, hipStream_t s);
