@@ -35,6 +35,19 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak, GB/s
 CALIB_BYTES = 1 << 30   # bytes read (and written) by the calibration copy
 
 
+def collection_forms(st) -> tuple[str, str]:
+    """Where a step object's residual collection runs, and what the residual-add call launches."""
+    from paper_2304_00737_amd import spardl
+    if not getattr(st, "fuse_collect", False):
+        return "its own call at the end of the step", "k_residual_add4<true, false>"
+    if spardl.collect_in_add(st.rows, st.P, st.n, st.k_blk):
+        return ("inside the next step's residual add",
+                "k_residual_add4<true, true> (the previous step's collection in its tiles)")
+    return ("in the next step's residual-add call, in kernels before the add",
+            "k_residual_add4<true, false> and, before it in the same call, the previous step's collection "
+            "(k_grc_zero, k_grc_drops)")
+
+
 def _kernel_src_hash() -> str:
     """Hash of the residual-add kernel's source (its file, with its launcher,
     and the headers it includes), to tell whether stored counter readings
@@ -443,12 +456,8 @@ def main() -> int:
                    "segments": len(wl.seg_len), "seed": W.SEED_BASE, "variant": args.variant, "teams": d,
                    "team_join": ("B-SAG" if args.bruck else "R-SAG") if d > 1 else None,
                    "L_per_team_block": st.k_blk if d > 1 else None,
-                   "residual_collection": ("inside the next step's residual add" if getattr(st, "fuse_collect", False)
-                                           else "its own call at the end of the step")},
-        "roofline": {"bound": "hbm", "kernel": (("k_residual_add4 (the previous step's collection in its tiles or, by size and "
-                                                  "density, in kernels of the same call before it)"
-                                                  if getattr(st, "fuse_collect", False) else "k_residual_add4<true, false>")
-                                                 if dominant == "residual_add" else dominant),
+                   "residual_collection": collection_forms(st)[0]},
+        "roofline": {"bound": "hbm", "kernel": collection_forms(st)[1] if dominant == "residual_add" else dominant,
                      "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "alg_bytes_per_launch": alg[dominant], "avg_launch_ms": dom_ms,
@@ -636,14 +645,11 @@ def per_worker_measure(wl, dev, steps: int, warmup: int, R: int, lazy: bool, fus
         "config": {"workload": wl.name, "P": P, "n_per_worker": n, "density": f"{wl.density[0]}/{wl.density[1]}",
                    "k_per_block": kb, "gradient_batches": wl.steps, "residual": "carried across steps",
                    "segments": len(wl.seg_len), "seed": W.SEED_BASE, "variant": "lazy" if lazy else "eager",
-                   "residual_collection": ("inside the next step's residual add" if getattr(st, "fuse_collect", False)
-                                           else "its own call at the end of the step"),
+                   "residual_collection": collection_forms(st)[0],
                    "timing": "ms_per_step: sum of the event-timed hot calls; span_ms_per_step: the whole step's "
                              "span on the stream less the gradient generation inside it; the workers' gradients "
                              f"are generated on the GPU between their calls, {R} rows per call ({R}-row workspace)"},
-        "roofline": {"bound": "hbm", "kernel": ("k_residual_add4 (the previous step's collection in its tiles or, by size and "
-                                                "density, in kernels of the same call before it)"
-                                                if getattr(st, "fuse_collect", False) else "k_residual_add4<true, false>"),
+        "roofline": {"bound": "hbm", "kernel": collection_forms(st)[1],
                      "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                      "alg_bytes_per_launch": alg_add, "avg_launch_ms": add_launch_ms},

@@ -163,6 +163,12 @@ int spardl_residual_add_collect(float* acc, int64_t ld_acc, const float* grad, i
                                 const float* const* drop_val, const int32_t* const* drop_cnt, void* ws,
                                 size_t ws_bytes, hipStream_t stream);
 
+/* Whether spardl_residual_add_collect over nworkers rows applies the
+ * collection to the add's tiles (1) or runs it in kernels of its own before
+ * the add (0; large sparse steps); the results are the same.  Host only.
+ * EINVAL on invalid sizes (as spardl_workspace_bytes). */
+int spardl_collect_in_add(int32_t nworkers, int32_t P, int64_t n, int32_t k_blk);
+
 /* The first half of a residual collection left to the next add: for the
  * rows w0 .. w0 + nworkers - 1, every SRS step and every add tile, the range
  * of the row's drops inside the tile, written into ws (the drop lists are

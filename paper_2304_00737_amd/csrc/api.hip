@@ -564,6 +564,11 @@ int spardl_residual_add_collect(float* acc, int64_t ld_acc, const float* grad, i
   return SPARDL_OK;
 }
 
+int spardl_collect_in_add(int32_t nworkers, int32_t P, int64_t n, int32_t k_blk) {
+  if (!sizes_ok(P, n, k_blk) || nworkers < 1 || nworkers > P) return SPARDL_EINVAL;
+  return collect_in_add(nworkers, P, n, k_blk, steps_of(P)) ? 1 : 0;
+}
+
 int spardl_residual_collect_index(int32_t w0, int32_t nworkers, int64_t n, int32_t P, int32_t k_blk,
                                   const int32_t* const* drop_idx, const int32_t* const* drop_cnt, void* ws,
                                   size_t ws_bytes, hipStream_t stream) {

@@ -40,6 +40,7 @@ _lib.spardl_workspace_init.restype = ctypes.c_int
 _lib.spardl_residual_add.argtypes = [_p, _i64, _p, _i64, _i32, _i32, _i64, _i32, _i32, _p, _sz, _p]
 _lib.spardl_residual_add_collect.argtypes = [_p, _i64, _p, _i64, _i32, _i32, _i64, _i32, _i32, _p, _p, _p, _p, _p, _p,
                                              _sz, _p]
+_lib.spardl_collect_in_add.argtypes = [_i32, _i32, _i64, _i32]
 _lib.spardl_residual_collect_index.argtypes = [_i32, _i32, _i64, _i32, _i32, _p, _p, _p, _sz, _p]
 _lib.spardl_block_topk.argtypes = [_p, _i64, _i32, _i32, _i64, _i32, _i32, _i32, _p, _p, _p, _p, _sz, _p]
 _lib.spardl_sparse_merge_topk.argtypes = [_p, _p, _i32, _i64, _i32, _i32, _p, _p, _p, _p, _sz, _p]
@@ -66,7 +67,7 @@ _lib.spardl_bsag_workspace_bytes.restype = _sz
 _lib.spardl_bsag_workspace_init.argtypes = [_i32, _i32, _i64, _i32, _p, _sz, _p]
 _lib.spardl_bsag_exchange.argtypes = [_p, _p, _i32, _i32, _i64, _i32, _p, _p, _p, _p, _p, _sz, _p]
 _lib.spardl_bsag_residual.argtypes = [_p, _i64, _i32, _i32, _i64, _i32, _p, _p, _p, _p, _p]
-for _f in ("residual_add", "residual_add_collect", "residual_collect_index", "block_topk", "sparse_merge_topk", "sparse_merge_topk_noalloc", "allgather_densify", "residual_collect",
+for _f in ("residual_add", "residual_add_collect", "collect_in_add", "residual_collect_index", "block_topk", "sparse_merge_topk", "sparse_merge_topk_noalloc", "allgather_densify", "residual_collect",
            "lazy_topk", "lazy_receive", "lazy_residual_collect", "rsag_workspace_init", "rsag_merge_topk",
            "rsag_residual", "bsag_workspace_init", "bsag_exchange", "bsag_residual", "team_workspace_init",
            "team_residual_add", "team_block_topk", "team_merge_topk", "team_residual_collect"):
@@ -156,6 +157,14 @@ def residual_add_collect(acc, grad, nworkers: int, n: int, P: int, ws, k_blk: in
     _check("residual_add_collect", _lib.spardl_residual_add_collect(
         _ptr(acc), ld_acc, _ptr(grad), ld_grad, w0, nworkers, n, P, k_blk, _ptr(local_idx), _ptr(member),
         arr(drop_idx), arr(drop_val), arr(drop_cnt), _ptr(ws), _nb(ws), _stream(stream)))
+
+
+def collect_in_add(nworkers: int, P: int, n: int, k_blk: int) -> bool:
+    """Whether residual_add_collect over these rows collects in the add's tiles (else in kernels before it)."""
+    r = _lib.spardl_collect_in_add(nworkers, P, n, k_blk)
+    if r < 0:
+        _check("collect_in_add", r)
+    return r == 1
 
 
 def residual_collect_index(w0: int, nworkers: int, n: int, P: int, k_blk: int, drop_idx, drop_cnt, ws, *,
@@ -375,7 +384,7 @@ def ws_layout(P: int, n: int, kb: int, ws_bytes: int) -> dict:
     L["keep"] = off; off += al(P * P * 4 * 4)             # the block top-k's selection rule per (worker, block)
     L["dtile"] = off; off += al(sum(P * m for m in bags) * add_tiles * 8)   # per (step, pair, add tile)
     L["sel"] = off                                        # the selected indices, where the residual collection may
-    if P * n >= max(l, 1) << 23 and (64 if l > 1 else 128) * kb * P <= n:   # run in kernels before the next add
+    if not collect_in_add(P, P, n, kb):                   # run in kernels before the next add
         off += al(P * P * kb * 4)
     L["fixed_end"] = off
     L["cand_entries"] = max(P * n, pairs_max * tiles_mg * 4096)

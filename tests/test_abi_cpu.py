@@ -302,3 +302,17 @@ def test_ws_layout_mirror():
                      (32, 1_500_000_000, 46_875)]:
         L = ws_layout(P, n, kb, 0)
         assert L["fixed_end"] + 3 * al(L["cand_entries"] * 4) == lib.spardl_workspace_bytes(P, P, n, kb), (P, n, kb)
+
+
+def test_collect_in_add_query():
+    """Both sides of the sizes, densities and rows per call where the deferred
+    collection changes its form; EINVAL on invalid sizes."""
+    q = lambda nw, P, n, kb: _lib().spardl_collect_in_add(ctypes.c_int32(nw), ctypes.c_int32(P), ctypes.c_int64(n),
+                                                          ctypes.c_int32(kb))
+    M = 1 << 23   # elements per call and SRS step
+    assert q(2, 2, M // 2, 10) == 0 and q(2, 2, M // 2 - 1, 10) == 1
+    assert q(8, 8, 3 * M // 8, 10) == 0 and q(7, 8, 3 * M // 8, 10) == 1
+    assert q(1, 32, 5 * M, 10) == 0 and q(1, 32, 5 * M - 1, 10) == 1 and q(2, 32, 5 * M - 1, 10) == 0
+    assert q(8, 8, 8 * M, M // 64) == 0 and q(8, 8, 8 * M, M // 64 + 1) == 1
+    assert q(2, 2, 2 * M, M // 128) == 0 and q(2, 2, 2 * M, M // 128 + 1) == 1
+    assert q(0, 4, 100, 3) == q(5, 4, 100, 3) == q(1, 4, 3, 1) == q(1, 4, 100, 26) == -1

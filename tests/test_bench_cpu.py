@@ -52,3 +52,20 @@ def test_cpu_baseline_reports_its_sample():
     assert out["cores"] == min(os.cpu_count(), bench.CPU_SHARE) and out["nproc"] == os.cpu_count()
     assert out["value"] > 0 and out["single_thread_value"] > 0 and out["cpu_model"]
     assert "block indices" in out["sample"] and "single-thread" in out["sample"]
+
+
+def test_records_name_the_collection_that_ran():
+    """The default, VGG-, BERT- and one-row GPT-2-XL-sized steps collect in
+    kernels before the add, a small one in its tiles; without the deferred
+    collection it is a call of its own."""
+    from types import SimpleNamespace
+
+    from paper_2304_00737_amd import workloads as W
+    for i, rows, want in [(1, 4, "inside"), (2, 8, "before the add"), (3, 8, "before the add"), (4, 16, "before the add"),
+                          (5, 1, "before the add")]:
+        wl = W.config(i)
+        st = SimpleNamespace(fuse_collect=True, rows=rows, P=wl.P, n=wl.n, k_blk=wl.k_blk)
+        where, kernel = bench.collection_forms(st)
+        assert want in where, (i, where)
+        assert ("k_grc_zero" in kernel) == (want != "inside")
+        assert "its own call" in bench.collection_forms(SimpleNamespace(**{**vars(st), "fuse_collect": False}))[0]
