@@ -106,8 +106,10 @@ __host__ __device__ __forceinline__ int64_t blk_start(int64_t b, int64_t n, int6
 // 64-bit division (a long scalar sequence per wave) precedes their loads.
 // For P <= START_MUL_MAX the quotient floor(x / P) of x = b r < P^2 is the high
 // word of x inv with inv = floor(2^32 / P) + 1: inv P exceeds 2^32 by at most
-// P, so the product exceeds 2^32 (x / P) by at most x < 2^32 / P (a division
-// is some 25 vector instructions, in every wave).
+// P, so the product exceeds 2^32 (x / P) by at most x < 2^32 / P.  (A division
+// is some 25 vector instructions in every wave before its loads: the fused add
+// of 8 rows of 25.6M takes 431 us with it and 422 without, of 16 rows of 16M
+// 498 and 481, the top-k after them 76 and 73, 38 and 35.)
 constexpr uint32_t START_MUL_MAX = 1024;
 struct Blocks {
   uint32_t n, P, q, r, inv;
@@ -147,7 +149,7 @@ __host__ __device__ __forceinline__ int64_t add_tiles_per_block(int64_t maxlen) 
 }
 
 // Level-1 histogram copies of each of the P blocks of a row of n elements:
-// every add tile flushes its histogram into copy (workgroup mod copies), and
+// every add tile flushes its histogram into copy (tile mod copies), and
 // the flushes into one copy serialise on its words, so a block has a copy per
 // ~512 of its add tiles (a power of two in [HCOPIES_MIN, HCOPIES_MAX]); the
 // level-1 select sums them.  Other writers use the first HCOPIES_MIN copies.
@@ -372,109 +374,6 @@ __device__ __forceinline__ void g2lds(uint32_t* lds, const uint32_t* __restrict_
     const int i = threadIdx.x + u * blockDim.x;
     if (i < count) lds[i] = r[u];
   }
-}
-
-// ---------------------------------------------------------------- cooperative searches
-// Number of leading positions p in [lo, hi) for which the monotone predicate
-// pred(p) holds (true ... true false ... false), found by the whole workgroup
-// with a (blockDim+1)-ary search: every round tests blockDim points at once,
-// so a range of 2^15 needs two rounds of loads.  `cnt` needs blockDim/64 + 1
-// words of LDS.  Contains barriers; every thread gets the answer.
-template <typename Pred>
-__device__ __forceinline__ int32_t wg_partition_point(int32_t lo, int32_t hi, Pred pred, uint32_t* cnt) {
-  const int nt = blockDim.x;
-  const int nw = nt / WAVE;
-  while (hi > lo) {
-    const int32_t S = hi - lo;
-    int32_t p;
-    bool active;
-    if (S <= nt) {
-      p = lo + (int32_t)threadIdx.x;
-      active = (int32_t)threadIdx.x < S;
-    } else {
-      p = lo + (int32_t)(((int64_t)S * (threadIdx.x + 1)) / (nt + 1));
-      active = true;
-    }
-    const bool t = active && pred(p);
-    const uint64_t m = __ballot(t);
-    if (lane_id() == 0) cnt[wave_id()] = popc64(m);
-    __syncthreads();
-    int32_t c = 0;
-    for (int i = 0; i < nw; ++i) c += (int32_t)cnt[i];
-    __syncthreads();
-    if (S <= nt) {
-      lo += c;
-      hi = lo;
-    } else {
-      const int32_t new_lo = c == 0 ? lo : lo + (int32_t)(((int64_t)S * c) / (nt + 1)) + 1;
-      const int32_t new_hi = c == nt ? hi : lo + (int32_t)(((int64_t)S * (c + 1)) / (nt + 1));
-      lo = new_lo;
-      hi = new_hi;
-    }
-  }
-  return lo;
-}
-
-// Two independent partition points found together: every round tests
-// blockDim points of each range, so both searches share their rounds of loads
-// and barriers.  `cnt` needs 2 (blockDim/64) words of LDS.
-template <typename Pred0, typename Pred1>
-__device__ __forceinline__ void wg_partition_point2(int32_t lo0, int32_t hi0, Pred0 pred0, int32_t lo1, int32_t hi1,
-                                                    Pred1 pred1, uint32_t* cnt, int32_t* r0, int32_t* r1) {
-  const int nt = blockDim.x;
-  const int nw = nt / WAVE;
-  auto probe = [&](int32_t lo, int32_t hi, int32_t* p, bool* active) {
-    const int32_t S = hi - lo;
-    if (S <= nt) {
-      *p = lo + (int32_t)threadIdx.x;
-      *active = (int32_t)threadIdx.x < S;
-    } else {
-      *p = lo + (int32_t)(((int64_t)S * (threadIdx.x + 1)) / (nt + 1));
-      *active = true;
-    }
-  };
-  auto narrow = [&](int32_t* lo, int32_t* hi, int32_t c) {
-    const int32_t S = *hi - *lo;
-    if (S <= nt) {
-      *lo += c;
-      *hi = *lo;
-    } else {
-      const int32_t new_lo = c == 0 ? *lo : *lo + (int32_t)(((int64_t)S * c) / (nt + 1)) + 1;
-      const int32_t new_hi = c == nt ? *hi : *lo + (int32_t)(((int64_t)S * (c + 1)) / (nt + 1));
-      *lo = new_lo;
-      *hi = new_hi;
-    }
-  };
-  while (hi0 > lo0 || hi1 > lo1) {
-    int32_t p0 = 0, p1 = 0;
-    bool a0 = false, a1 = false;
-    if (hi0 > lo0) probe(lo0, hi0, &p0, &a0);
-    if (hi1 > lo1) probe(lo1, hi1, &p1, &a1);
-    const bool t0 = a0 && pred0(p0);
-    const bool t1 = a1 && pred1(p1);
-    const uint64_t m0 = __ballot(t0), m1 = __ballot(t1);
-    if (lane_id() == 0) {
-      cnt[wave_id()] = popc64(m0);
-      cnt[nw + wave_id()] = popc64(m1);
-    }
-    __syncthreads();
-    int32_t c0 = 0, c1 = 0;
-    for (int i = 0; i < nw; ++i) {
-      c0 += (int32_t)cnt[i];
-      c1 += (int32_t)cnt[nw + i];
-    }
-    __syncthreads();
-    if (hi0 > lo0) narrow(&lo0, &hi0, c0);
-    if (hi1 > lo1) narrow(&lo1, &hi1, c1);
-  }
-  *r0 = lo0;
-  *r1 = lo1;
-}
-
-// First position j in [0, len) with a[j] >= x (len if none); a sorted ascending.
-__device__ __forceinline__ int32_t wg_lower_bound(const int32_t* __restrict__ a, int32_t len, int64_t x,
-                                                  uint32_t* cnt) {
-  return wg_partition_point(0, len, [&](int32_t p) { return (int64_t)a[p] < x; }, cnt);
 }
 
 }  // namespace spardl

@@ -119,14 +119,11 @@ __device__ __forceinline__ void store_quad(float* __restrict__ p, f4v q, uint32_
 // start, row stride and base a multiple of 16 bytes): a float4 lies wholly
 // inside or outside the block and the masks cost nothing.  ROWS_SHORT: rows
 // of fewer than four elements, which no float4 load fits in.  A worker count
-// or a length that leaves ragged blocks thus keeps the candidates and the
-// fused collection: a step of P = 14 workers with n = 20,033,001 took 1224 us
-// when such rows had a scalar add without candidates and a second read of
-// every block, and 917 us this way; with P = 6, n = 14,715,999 and 10 %
-// density 857 and 765 us.
-enum RowKind : int { ROWS_EVEN, ROWS_RAGGED, ROWS_SHORT };
-constexpr int ADD_STAGE = 512;          // speculative candidates (or drops) staged in LDS per tile
-
+// or a length that leaves ragged blocks thus keeps the candidates: a step of P =
+// 14 workers with n = 20,033,001 took 1224 us when such rows had a scalar add
+// without candidates and a second read of every block, and 917 us this way; with
+// P = 6, n = 14,715,999 and 10 % density 857 and 765 us (both before the choices
+// below; 870 and 670 with them).
 //
 // Without COLL a tile has 512 threads of one float4 each: an in-place add on
 // its own streams faster so (0.2G elements 387 against 396 us, 1.76G 3377
@@ -137,6 +134,8 @@ constexpr int ADD_STAGE = 512;          // speculative candidates (or drops) sta
 // 6 ragged rows of 14.7M at 10 % 251 -> 251 -> 226.  With COLL the collection's
 // instructions and barriers per wave weigh more than that: 415 us for 8 rows of
 // 25.6M with 256 threads, 483 with 512, and contiguous runs cost 4-8 %.
+enum RowKind : int { ROWS_EVEN, ROWS_RAGGED, ROWS_SHORT };
+constexpr int ADD_STAGE = 512;          // speculative candidates (or drops) staged in LDS per tile
 constexpr int add_threads(bool coll) { return coll ? 256 : 512; }
 
 template <bool HIST, bool COLL, int ROWS>
@@ -401,7 +400,7 @@ __global__ __launch_bounds__(add_threads(COLL)) void k_residual_add4(float* __re
     }
   }
   float r[4 * F4];
-  uint32_t packed = 0;   // candidates of chunk 0 | chunk 1 << 16 (at most 1024 each)
+  uint32_t packed = 0;   // candidates of chunk 0 | chunk 1 << 16 (a tile holds at most CH of each)
 #pragma unroll
   for (int j = 0; j < F4; ++j) {
     if (in[j]) {
@@ -440,7 +439,9 @@ __global__ __launch_bounds__(add_threads(COLL)) void k_residual_add4(float* __re
     tot += x;
   }
   {
-    uint32_t* __restrict__ H = sp.hist1 + ((int64_t)wb * sp.hcopies + (g & (sp.hcopies - 1u))) * NB1;   // a power of 2
+    // (the copies, a power of 2, in tile order: by order of dispatch, which takes a tile of each XCD in turn, 8
+    // rows of 25.6M take 466 us instead of 420)
+    uint32_t* __restrict__ H = sp.hist1 + ((int64_t)wb * sp.hcopies + (g & (sp.hcopies - 1u))) * NB1;
     if (M.fine) flush_hist<NT, NB_FLOOR>(h, H);   // uniform
     else flush_hist<NT>(h, H);
   }

@@ -245,8 +245,10 @@ def test_step_fused_collect(P, n, kb, kind, steps, rows):
     """The residual collection left to the next step's add: after every add,
     acc equals the oracle's residual plus the gradient, bit for bit; every
     step's selections, drops and update are the oracle's; flush() leaves the
-    last residual.  rows: workers per call (0: all); rows the float4 add does
-    not take run the separate collection inside the same call."""
+    last residual.  rows: workers per call (0: all).  At these sizes the
+    collection runs in the add's tiles (large sparse steps, collected by
+    kernels before it, are held against a collection of its own in
+    test_gpu_ragged.py and against full-size checksums)."""
     if rows > P:
         pytest.skip("fewer workers than rows per call")
     log(f"step fused collect P={P} n={n} kb={kb} kind={kind} steps={steps + 1} rows={rows}")
