@@ -51,21 +51,25 @@ struct Layout {
 // Whether an add over nworkers rows applies the previous step's residual
 // collection to its tiles (k_residual_add4 with COLL); otherwise the
 // collection's own kernels run before the plain add, with the same results.
-// In the tiles it costs time per element streamed, on its own a launch per SRS
-// step and one more, and time per entry selected or dropped, scattered: so it
-// goes into the add for calls of fewer than 8M elements per SRS step, and for
-// dense ones.  Whole steps in us, in the tiles and apart, all rows in one call:
-// P = 2, 0.1 %, n = 4M 75 and 78, 8M 121 and 117; P = 4, 0.1 %, n = 4M 99 and
-// 100, 8M 155 and 152; P = 8, 1 %, n = 2M 126 and 130, 4M 204 and 200, 25.6M
-// 679 and 646; P = 16, 1 %, n = 1M 110 and 118, 2M 167 and 167, 4M 266 and 249.
-// One row per call: P = 8, n = 25.6M at 1 % 1040 and 1019; P = 16, n = 30M at
-// 1 % 2043 and 2091, 60M at 0.1 % 3008 and 2907; P = 32, n = 40M at 0.1 % 3858
-// and 3955 (two rows 3351 and 3268).  Densities of 1.6, 3 and 10 %: P = 4, n =
-// 32M 521 and 494, 578 and 578, 905 and 979; P = 16, n = 4M 292 and 276, 347 and
-// 334, 471 and 517; P = 2, n = 64M at 0.1 and 1 % 425 and 413, 474 and 487.
+// In the tiles it costs time per element streamed, on its own time per entry
+// selected or dropped, scattered, and a launch per SRS step and one more: so it
+// goes into the add for small steps, for calls of few elements, and for dense
+// steps.  Whole steps in us, in the tiles and apart, on gradients of 160 layers
+// of different scale.  All rows in one call: P = 2, n = 32M at 0.1 and 1 % 244
+// and 244, 265 and 270, 64M 412 and 406, 444 and 452; P = 4, n = 16M 212 and
+// 217, 242 and 251, 32M 399 and 391, 435 and 438, 64M 695 and 679, 767 and 767;
+// P = 8, n = 16M 332 and 338, 414 and 425, 32M 646 and 627, 727 and 724; P = 16,
+// n = 8M 319 and 330, 440 and 454, 16M 584 and 581, 743 and 761, 32M 1139 and
+// 1094, 1357 and 1352.  (Without layers, where selections are spread evenly, apart
+// gains from a quarter of these sizes on: P = 8, n = 4M at 1 % 204 and 200.)  Some
+// rows at a time, 48 layers: P = 32, n = 40M at 0.1 %, one row 3667 and 3815, two
+// 3231 and 3166; P = 16, one row of 30M at 1 % 2187 and 2288, of 60M at 0.1 % 2876
+// and 2820; P = 8, n = 25.6M at 1 %, one row 1121 and 1151, two 879 and 858.
+// Densities of 1.6, 3 and 10 %, no layers: P = 4, n = 32M 521 and 494, 578 and
+// 578, 905 and 979.
 bool collect_in_add(int32_t nworkers, int32_t P, int64_t n, int32_t kb, int32_t l) {
   if (l > COLLECT_MAX_STEPS) return false;   // more SRS steps than the add takes
-  return (int64_t)nworkers * n < (int64_t)std::max(l, 1) << 23 || (l > 1 ? 64ll : 128ll) * kb * P > n;
+  return (int64_t)P * n < (1ll << 27) || (int64_t)nworkers * n < (3ll << 24) || 64ll * kb * P > n;
 }
 
 // rows: rows of acc the calls cover (P, or all d teams' rows with P = Q

@@ -309,10 +309,8 @@ def test_collect_in_add_query():
     collection changes its form; EINVAL on invalid sizes."""
     q = lambda nw, P, n, kb: _lib().spardl_collect_in_add(ctypes.c_int32(nw), ctypes.c_int32(P), ctypes.c_int64(n),
                                                           ctypes.c_int32(kb))
-    M = 1 << 23   # elements per call and SRS step
+    M, R = 1 << 27, 3 << 24   # elements per step and per call
     assert q(2, 2, M // 2, 10) == 0 and q(2, 2, M // 2 - 1, 10) == 1
-    assert q(8, 8, 3 * M // 8, 10) == 0 and q(7, 8, 3 * M // 8, 10) == 1
-    assert q(1, 32, 5 * M, 10) == 0 and q(1, 32, 5 * M - 1, 10) == 1 and q(2, 32, 5 * M - 1, 10) == 0
-    assert q(8, 8, 8 * M, M // 64) == 0 and q(8, 8, 8 * M, M // 64 + 1) == 1
-    assert q(2, 2, 2 * M, M // 128) == 0 and q(2, 2, 2 * M, M // 128 + 1) == 1
+    assert q(1, 32, R, 10) == 0 and q(1, 32, R - 1, 10) == 1 and q(2, 32, R - 1, 10) == 0
+    assert q(8, 8, M, M // 512) == 0 and q(8, 8, M, M // 512 + 1) == 1
     assert q(0, 4, 100, 3) == q(5, 4, 100, 3) == q(1, 4, 3, 1) == q(1, 4, 100, 26) == -1

@@ -93,12 +93,11 @@ def test_collection_in_the_add_or_before_it(n, kb, rows):
     assert torch.equal(deferred.acc.view(torch.int32), own.acc.view(torch.int32)), "residual"
 
 
-# P, n, kb, rows per call: calls of 8M elements per SRS step, one less and a few more; densities of 1/128 (one SRS
-# step) and 1/64 and just above; rows a few at a time on both sides, an uneven last group in the tiles and the others not
-@pytest.mark.parametrize("P,n,kb,rows", [(2, 2 ** 22, 1000, 0), (2, 2 ** 22 - 1, 1000, 0), (2, 2 ** 22 + 1, 1000, 0),
-                                         (2, 2 ** 22, 2 ** 14, 0), (2, 2 ** 22, 2 ** 14 + 1, 0), (4, 2 ** 22, 1000, 0),
-                                         (4, 2 ** 22, 2 ** 14, 0), (4, 2 ** 22, 2 ** 14 + 1, 0), (4, 2 ** 22, 1000, 1),
-                                         (4, 2 ** 24, 1000, 1), (3, 2 ** 23, 1000, 2), (1, 2 ** 23, 9000, 0)])
+# P, n, kb, rows per call: calls of 3 2^24 elements (of steps of at least 2^27) and one less, a last group of fewer
+# rows in the tiles and the others not, one worker
+@pytest.mark.parametrize("P,n,kb,rows", [(4, 3 * 2 ** 24, 1000, 1), (4, 3 * 2 ** 24 - 1, 1000, 1), (3, 3 * 2 ** 24 + 1, 1000, 2),
+                                         (5, 2 ** 25, 1000, 2), (5, 2 ** 25, 2 ** 16, 3), (8, 2 ** 24, 1000, 2),
+                                         (8, 2 ** 24, 1000, 3), (1, 2 ** 27, 9000, 0), (1, 2 ** 27 - 1, 9000, 0)])
 def test_collection_in_the_add_or_before_it_by_rows(P, n, kb, rows):
     """The route of the deferred collection follows the rows of the call (its
     index is built for all of them): the same steps as with the collection as
