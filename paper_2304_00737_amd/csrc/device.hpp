@@ -7,6 +7,7 @@ namespace spardl {
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // a float4 at any dword address
+typedef int32_t i4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Adds the non-zero bins of an LDS histogram of NB bins into a global one,
 // by a workgroup of NT threads.  Consecutive lanes take consecutive bins
