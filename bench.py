@@ -183,8 +183,8 @@ def main() -> int:
                     help="workload 5: workers per residual-add / block top-k call (default PER_WORKER_ROWS)")
     ap.add_argument("--separate-collect", action="store_true",
                     help="eager variant: run the global residual collection as its own call at the end of "
-                         "each step (by default it runs inside the next step's residual add, which reads "
-                         "and writes every element of the residual anyway)")
+                         "each step (by default the next step's residual-add call runs it, in the add's "
+                         "tiles or, for large sparse steps, in kernels before the add)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extra", action="store_true",
                     help="skip the GPT-2-XL-sized and HIP-graph sub-objects of the default run")

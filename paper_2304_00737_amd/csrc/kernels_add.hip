@@ -123,7 +123,7 @@ __device__ __forceinline__ void store_quad(float* __restrict__ p, f4v q, uint32_
 // 14 workers with n = 20,033,001 took 1224 us when such rows had a scalar add
 // without candidates and a second read of every block, and 917 us this way; with
 // P = 6, n = 14,715,999 and 10 % density 857 and 765 us (both before the choices
-// below; 870 and 670 with them).
+// below; 832 and 678 with them).
 //
 // Without COLL a tile has 512 threads of one float4 each: an in-place add on
 // its own streams faster so (0.2G elements 387 against 396 us, 1.76G 3377
