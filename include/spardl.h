@@ -137,12 +137,13 @@ int spardl_residual_add(float* acc, int64_t ld_acc, const float* grad, int64_t l
                         hipStream_t stream);
 
 /* The previous step's global residual collection (Sec. III-C) and this
- * step's residual add (Algorithm 1, G + xi) in one pass over acc: the same
+ * step's residual add (Algorithm 1, G + xi) in one pass over acc, or for
+ * large sparse steps (spardl_collect_in_add) one after the other: the same
  * acc, bit for bit, as spardl_residual_collect(..., member) followed by
  * spardl_residual_add with ws, and the same histograms and candidates for
- * spardl_block_topk(SPARDL_TOPK_HIST_READY) after it.  Each tile of acc is
- * read once and written once, whole; the separate collection writes single
- * words all over acc instead.
+ * spardl_block_topk(SPARDL_TOPK_HIST_READY) after it.  In one pass each tile
+ * of acc is read once and written once, whole; the separate collection writes
+ * single words all over acc instead.
  * The zeroing half finds a worker's selections from the values themselves:
  * the previous step's spardl_block_topk on these rows, with this ws, keeps
  * each block's selection rule in ws, so acc must be unchanged since that
