@@ -320,8 +320,8 @@ int topk_units(const float* acc, int64_t ld_acc, int64_t units, const Units& U, 
   }
   if (one) {
     SPARDL_TRY(launch_topk_one(acc, ld_acc, units, U, n, P, k_blk, smax, (int32_t)L.add_tiles, spec, w.hist1, w.state,
-                               hint, w.spec_used, w.spec_cnt, w.slot_cnt, w.slot_nbin, w.cand_idx, w.cand_val, w.bin_key,
-                               sp_idx, sp_val, local_idx, keep, sel, w.err, stream));
+                               hint, w.spec_used, w.spec_cnt, w.slot_cnt, w.slot_nbin, w.cand_idx, w.cand_val, sp_idx,
+                               sp_val, local_idx, keep, sel, w.err, stream));
     return SPARDL_OK;
   }
   // hist1: the staged threshold for long units builds its level-2/3 histograms in the units'

@@ -24,10 +24,10 @@ namespace spardl {
 // The block's histogram is the sum of its hc copies (hist_copies_for);
 // four copies' loads are in flight at a time.  The copies are cleared once read (the
 // workspace keeps its histograms at zero between steps).  A histogram of the
-// fused add covers keys at or above hist_floor(its candidate floor) in fine
-// bins (L1Map in device.hpp), which decides the select exactly whenever the
-// threshold bin lies inside that window; otherwise the workgroup rebuilds the
-// block's full histogram of the top 12 key bits from acc.  A full histogram
+// fused add covers keys at or above hist_floor(its candidate floor) in the
+// bins of L1Map (device.hpp), which decide the select exactly unless the
+// threshold fell below that floor or rose into the last bin; then the workgroup
+// rebuilds the block's full histogram of the top 12 key bits from acc.  A full histogram
 // must hold exactly the block's entries.  The threshold bin goes to the state
 // as a key prefix and its shift (ST_T1, ST_SHIFT).
 struct Level1 {
@@ -77,7 +77,7 @@ __device__ __forceinline__ Level1 block_level1(uint32_t* __restrict__ H, uint32_
   R.full = !M.fine;   // the top-12-bit histogram of every key
   R.pfx = T;
   R.S = D1_SHIFT;
-  // the threshold fell below the histogram's floor, or above its fine window:
+  // the threshold fell below the histogram's floor, or rose into its last bin:
   // count the whole block by its top 12 key bits
   if (!R.full && (!R.ok || !M.bin_keys(T, &R.pfx, &R.S))) {
     for (int i = threadIdx.x; i < NB1; i += NT) h[i] = 0u;
@@ -1863,7 +1863,7 @@ struct TopkOne {
   uint32_t kb, smax, add_tiles, hc;
   int spec;
   uint32_t *hist1, *state, *spec_t1, *keep, *err;
-  const uint32_t *spec_used, *spec_cnt, *slot_cnt, *slot_nbin, *bin_key;
+  const uint32_t *spec_used, *spec_cnt, *slot_cnt, *slot_nbin;
   int32_t* cand_idx;
   float* cand_val;
   int32_t *out_idx, *local_idx, *sel;
@@ -2164,8 +2164,7 @@ hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, con
                            int32_t kb, int32_t smax, int32_t add_tiles, bool spec, uint32_t* hist1, uint32_t* state,
                            uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt,
                            const uint32_t* slot_cnt, const uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val,
-                           const uint32_t* bin_key, int32_t* out_idx, float* out_val, int32_t* local_idx,
-                           uint32_t* keep, int32_t* sel, uint32_t* err, hipStream_t s) {
+                           int32_t* out_idx, float* out_val, int32_t* local_idx, uint32_t* keep, int32_t* sel, uint32_t* err, hipStream_t s) {
   TopkOne a;
   a.acc = acc;
   a.ld_acc = ld_acc;
@@ -2185,7 +2184,6 @@ hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, con
   a.spec_cnt = spec_cnt;
   a.slot_cnt = slot_cnt;
   a.slot_nbin = slot_nbin;
-  a.bin_key = bin_key;
   a.cand_idx = cand_idx;
   a.cand_val = cand_val;
   a.out_idx = out_idx;

@@ -68,8 +68,7 @@ hipError_t launch_topk_one(const float* acc, int64_t ld_acc, int64_t nunits, con
                            int32_t kb, int32_t smax, int32_t add_tiles, bool spec, uint32_t* hist1, uint32_t* state,
                            uint32_t* spec_t1, const uint32_t* spec_used, const uint32_t* spec_cnt,
                            const uint32_t* slot_cnt, const uint32_t* slot_nbin, int32_t* cand_idx, float* cand_val,
-                           const uint32_t* bin_key, int32_t* out_idx, float* out_val, int32_t* local_idx,
-                           uint32_t* keep, int32_t* sel, uint32_t* err, hipStream_t s);
+                           int32_t* out_idx, float* out_val, int32_t* local_idx, uint32_t* keep, int32_t* sel, uint32_t* err, hipStream_t s);
 hipError_t launch_collect(const float* acc, int64_t ld_acc, int64_t nunits, const Units& U, int64_t n, int32_t P,
                           int32_t kb, int32_t smax, const uint32_t* state, const uint32_t* spec_cnt,
                           int32_t add_tiles, uint32_t* slot_cnt, uint32_t* slot_nbin, int32_t* cand_idx,
